@@ -3,10 +3,11 @@
 // request, fresh rows for masked tokens and cached rows for the others (the
 // LLM-decoding analogy of that subsection). Softmax is the full, unmasked one.
 //
-// Workgroup = (query tile of 64 packed rows of one segment, head); four
-// waves, sixteen queries each. Key/value tiles of 64 tokens are staged in
-// LDS and shared by the four waves. Online softmax in float32 with exp2 and a
-// log2(e)-prescaled score.
+// Two kernels, one for bf16 (further down) and one for float32: workgroup =
+// (query tile of 64 packed rows of one segment, head); four waves, sixteen
+// queries each. Key/value tiles of 64 tokens are staged in LDS and shared by
+// the four waves. Online softmax in float32 with exp2 and a log2(e)-prescaled
+// score.
 //
 // MFMA orientation: the scores are computed transposed, S^T = K Q^T, so each
 // lane holds one query column and four keys per 16-key subtile. That is
@@ -15,7 +16,7 @@
 // A operand (V^T rows) reads contiguous keys. The pairing of MFMA K-slots to
 // keys only has to agree between the two operands of one instruction, which
 // it does by construction.
-#include <cstdlib>
+#include <algorithm>
 
 #include "common.h"
 #include "kernels.h"
@@ -213,13 +214,8 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(AttnDesc a) {
 __device__ __forceinline__ f32x4_t mfma32(bf16x8_t a, bf16x8_t b, f32x4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ f32x4_t mfma16(bf16x4_t a, bf16x4_t b, f32x4_t c) {
-    typedef short s4 __attribute__((ext_vector_type(4)));
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s4, a), __builtin_bit_cast(s4, b), c, 0, 0, 0);
-}
-
 // ---------------------------------------------------------------------------
-// bf16 kernel for head_dim 64 / 72 / 128.
+// bf16 kernel, head_dim any multiple of 8 up to 128.
 //
 // Workgroup = 128 packed query rows of one segment x one head x one key range;
 // each wave owns 32 queries (two 16-query MFMA column blocks), so every K and
@@ -233,41 +229,72 @@ __device__ __forceinline__ f32x4_t mfma16(bf16x4_t a, bf16x4_t b, f32x4_t c) {
 // (i & 3) of the 8 bytes addressed by lane 4e + (i >> 2), e = 0..3. Each
 // lane therefore addresses V[key0 + (l16 >> 2)][hd0 + 4 (l16 & 3)] and
 // receives V[key0 + e][hd0 + l16], e = 0..3: four keys of one head_dim row,
-// in the k-slot order of P^T. Rows of 128 / 256 bytes carry their 16-byte
-// chunks XOR-swizzled by dma_swz(row) so both the K fragment reads (16 rows)
-// and the transpose reads (8 rows x 32 bytes per half wave) are conflict-free;
-// 144-byte rows (head_dim 72) need no swizzle. Keys past the end read as
-// zeros (buffer bound). The softmax denominator comes from V^T rows of ones:
-// a constant operand for head_dim 64 / 128, and for head_dim 72 the padding
-// rows 72..79, whose lanes address a small LDS block of ones.
+// in the k-slot order of P^T. Keys past the end read as zeros (buffer bound).
+// The softmax denominator comes from V^T rows of ones: a constant operand
+// where head_dim is a multiple of 16, else the padding rows of the last
+// 16-row block, whose lanes address a small LDS block of ones.
+//
+// LDS banks: a ds_read_b128 is served in groups of 16 lanes (0-3, 12-15 and
+// 20-27; 4-11, 16-19 and 28-31; the same of the upper half), so a K fragment
+// read (16 rows, chunk g of lane group g) mixes two chunk columns. k_swz XORs
+// the 16-byte chunks of a row so that each group falls into 16 different bank
+// groups at every even chunk count (head_dim 64: 4.6 cycles per read, 8.4 with
+// a swizzle that only separates the 16 rows of one column); odd counts (72,
+// 104, ...) stay two-way. The transpose reads take 4 rows x 32 bytes per
+// 16-lane group, which v_swz keeps apart for rows of 128 and 256 bytes.
+//
+// What bounds it: at two or three workgroups per CU the matrix cores are busy
+// 40-50% of the time, the rest is the softmax (per 64-key tile and wave 32
+// exponentials at 8.6 cycles and ~110 other VALU instructions at 3-5, against
+// 576 MFMA cycles at head_dim 64 and 1088 at 128), of which only a part runs
+// under another wave's MFMAs, and the start and end of each workgroup. The
+// running maximum is subtracted by starting the score accumulators at -m, and
+// its row reduction runs only when some lane's maximum calls for a rescale.
+// Measured at 4 x ~1450 rows of 24 heads of 128 over 4608 keys 364 -> 339 us,
+// 4096 rows of 16 heads of 72 over 4096 keys 103 (with combine) -> 95 us; the
+// head_dims that had a register-staged kernel before: 96 with 2.6k rows of 12
+// heads over 2745 keys 182 -> 62 us. 32 x 32 x 16 MFMAs with the denominator on
+// v_dot2 (a software pipeline over 32-key blocks, scheduled by hand or by the
+// compiler) were 10-20% slower.
 // ---------------------------------------------------------------------------
 
 constexpr float kRescaleLog2 = 8.0f;   // softmax weights may reach 2^8 before a rescale
 
 template <int HD>
 struct DmaCfg {
-    static constexpr int NK32 = HD / 32;
-    static constexpr bool K16 = (HD % 32) != 0;
+    // 32-deep QK steps; the last one's padding slots multiply zeros by zeros.
+    // (A 16-deep MFMA for a short remainder takes the same 16 cycles, and one
+    // that continued the accumulators of a 32-deep one right before it gave a
+    // query block wrong scores now and then: 390 of 1500 runs at head_dim 48.)
+    static constexpr int NK32 = (HD + 31) / 32;
     static constexpr int ROWB = HD * 2;                 // bytes per K / V row
-    static constexpr bool SWZ = ROWB == 128 || ROWB == 256;
+    static constexpr bool SWZ = ROWB == 128 || ROWB == 256;   // V rows swizzled
     static constexpr int TILEB = kKeyTile * ROWB;       // bytes per K (or V) tile
-    static constexpr int KPAD = 16;                     // past the K tile: head_dim 72 reads 8 B beyond a row
+    static constexpr bool KTAIL = HD % 32 != 0;         // the last QK step has padding slots
+    static constexpr int KPAD = 16;                     // zeros past the K tile, read by the padding slots
     static constexpr int STAGEB = 2 * TILEB + KPAD;     // K tile, pad, V tile
     static constexpr int INSTR = TILEB / 1024;          // 1 KB copies per tile
     static constexpr int NQ = 2 * INSTR;                // copies per stage (K then V)
-    static constexpr int IPW_MIN = NQ / 4;              // copies per wave per stage (fewest)
-    static constexpr int IPW_MAX = (NQ + 3) / 4;
+    static constexpr int IPW_MAX = (NQ + 3) / 4;       // copies per wave per stage (most)
     static constexpr bool SUM_IN_PAD = (HD % 16) != 0;
     static constexpr int NHS = (HD + 15) / 16 + (SUM_IN_PAD ? 0 : 1);
     static constexpr int NREAL = (HD + 15) / 16;        // O^T subtiles with V rows
     static_assert(TILEB % 1024 == 0, "tile copies");
 };
 
-// 16-byte chunk swizzle of a K / V row (see the kernel comment).
+// 16-byte chunk swizzles of a V and of a K row (XOR of the chunk index; see
+// the kernel comment).
 template <int ROWB>
-__device__ __forceinline__ int dma_swz(int r) {
+__device__ __forceinline__ int v_swz(int r) {
     if constexpr (ROWB == 128) return 2 * ((r >> 1) & 3) + ((r >> 3) & 1);
     else if constexpr (ROWB == 256) return 2 * (r & 7) + ((r >> 3) & 1);
+    else return 0;
+}
+template <int ROWB>
+__device__ __forceinline__ int k_swz(int r) {
+    if constexpr (ROWB == 256) return r & 15;
+    else if constexpr (ROWB == 128) return (r >> 1) & 7;
+    else if constexpr (ROWB % 128 == 64) return (r >> 1) & 3;
     else return 0;
 }
 
@@ -279,17 +306,18 @@ __device__ __forceinline__ bf16x4_t ld_tr16(lds_cptr p) {
     return __builtin_bit_cast(bf16x4_t, v);
 }
 
-// Workgroups per CU the register budget is set for: four for head_dim 64
-// (128 VGPRs, no spills), two for 72 and 128 (whose 140 / 208 VGPRs then
-// allow three and two).
-constexpr int dma_occupancy(int hd) { return hd == 64 ? 4 : 2; }
+// Workgroups per CU the register budget is set for: four up to head_dim 48
+// (128 VGPRs, no spills), three for 56 and 64, two above (whose registers then
+// allow two or three).
+constexpr int dma_occupancy(int hd) { return hd <= 48 ? 4 : hd <= 64 ? 3 : 2; }
 
-template <int HD, int S>
+template <int HD>
 __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_kernel(AttnDesc a) {
     using C = DmaCfg<HD>;
+    constexpr int S = 2;   // LDS stages
     __shared__ __attribute__((aligned(1024))) uint8_t smem[S * C::STAGEB + 16];
     const uint32_t lds0 = lds_addr(smem);
-    const uint32_t ones_rel = S * C::STAGEB;            // 8 bytes of bf16 ones (head_dim 72)
+    const uint32_t ones_rel = S * C::STAGEB;            // 8 bytes of bf16 ones (SUM_IN_PAD)
 
     const int tid = threadIdx.x;
     const int lane = tid % kWave;
@@ -316,7 +344,7 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
     const int kt1 = min(ntiles_all, kt0 + a.tiles_per_split);
     const int nt = max(0, kt1 - kt0);
 
-    // constant LDS: the K pads (finite bytes for the head_dim-72 over-read) and the ones block
+    // constant LDS: the K pads' zeros and the ones block
     if (tid < S) *reinterpret_cast<uint4*>(smem + tid * C::STAGEB + C::TILEB) = make_uint4(0u, 0u, 0u, 0u);
     if (tid == S) *reinterpret_cast<uint2*>(smem + S * C::STAGEB) = make_uint2(0x3f803f80u, 0x3f803f80u);
 
@@ -330,7 +358,7 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
         const bool isV = q >= C::INSTR;
         const int pos = (q % C::INSTR) * 1024 + lane * 16;
         const int r = pos / C::ROWB;
-        const int c = ((pos % C::ROWB) / 16) ^ dma_swz<C::ROWB>(r);
+        const int c = ((pos % C::ROWB) / 16) ^ (isV ? v_swz<C::ROWB>(r) : k_swz<C::ROWB>(r));
         voff[i] = (uint32_t)(r * 4 * d + (isV ? 2 * d : 0) + head * C::ROWB + c * 16);
         ldst[i] = __builtin_amdgcn_readfirstlane((uint32_t)((isV ? C::TILEB + C::KPAD : 0) + (q % C::INSTR) * 1024));
     }
@@ -343,8 +371,7 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
     };
 
     // Q^T fragments (B operand)
-    bf16x8_t qf[2][C::NK32 > 0 ? C::NK32 : 1];
-    bf16x4_t qf16[2];
+    bf16x8_t qf[2][C::NK32];
     const bf16_t* __restrict__ q = static_cast<const bf16_t*>(a.q);
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
@@ -354,25 +381,26 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
 #pragma unroll
         for (int kc = 0; kc < C::NK32; ++kc) {
             vec16 v = {{0u, 0u, 0u, 0u}};
-            if (valid) v = ld16(qp + kc * 32 + grp * 8);
+            if (valid && kc * 32 + grp * 8 < HD) v = ld16(qp + kc * 32 + grp * 8);
             qf[qb][kc] = __builtin_bit_cast(bf16x8_t, v);
-        }
-        if constexpr (C::K16) {
-            const int k = C::NK32 * 32 + grp * 4;
-            uint2 v = make_uint2(0u, 0u);
-            if (valid && k < HD) v = *reinterpret_cast<const uint2*>(qp + k);
-            qf16[qb] = __builtin_bit_cast(bf16x4_t, v);
         }
     }
 
     // fragment read offsets inside a stage (bytes)
-    const int fK = dma_swz<C::ROWB>(l16);
-    uint32_t koff[C::NK32 > 0 ? C::NK32 : 1];
+    const int fK = k_swz<C::ROWB>(l16);
+    uint32_t koff[C::NK32];
 #pragma unroll
     for (int kc = 0; kc < C::NK32; ++kc) koff[kc] = l16 * C::ROWB + (((4 * kc + grp) ^ fK) * 16);
-    const uint32_t koff16 = l16 * C::ROWB + C::NK32 * 64 + grp * 8;   // head_dim 72: 16-deep step
+    // last QK step of a head_dim that is not a multiple of 32, per 16-key
+    // block: lanes whose slots lie past the row read the stage's block of zeros
+    uint32_t kofft[C::KTAIL ? 4 : 1];
+    if constexpr (C::KTAIL) {
+        const int col = (C::NK32 - 1) * 64 + grp * 16;   // bytes
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) kofft[ks] = col < C::ROWB ? (ks * 16 + l16) * C::ROWB + col : C::TILEB;
+    }
     const int rowA = 4 * grp + (l16 >> 2);
-    const int fV = dma_swz<C::ROWB>(rowA);
+    const int fV = v_swz<C::ROWB>(rowA);
     uint32_t voffh[C::NREAL];
 #pragma unroll
     for (int h = 0; h < C::NREAL; ++h) {
@@ -386,28 +414,28 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
     for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
         for (int h = 0; h < C::NHS; ++h) oacc[qb][h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    float m_run[2] = {-INFINITY, -INFINITY};
-    const float cs = a.scale_log2;
+    const float cs = a.scale_log2, rescale_at = kRescaleLog2 / cs;
+    // running maximum per query, subtracted from the scores by starting their
+    // accumulators at -m
+    float m_run[2] = {0.f, 0.f};
+    f32x4_t negm[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
     const bf16x8_t onesf = __builtin_bit_cast(bf16x8_t, make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
 
-    // S^T of one tile (QK^T) into sacc, keys past T masked
+    // S^T - m of one tile (QK^T) into sacc, keys past T masked
     auto qk = [&](uint32_t sbase, int k0, bool tail, f32x4_t (&sacc)[2][4]) {
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) sacc[qb][ks] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int ks = 0; ks < 4; ++ks) sacc[qb][ks] = negm[qb];
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
 #pragma unroll
             for (int kc = 0; kc < C::NK32; ++kc) {
-                const bf16x8_t kf = *reinterpret_cast<const bf16x8_t*>(smem + sbase + koff[kc] + ks * 16 * C::ROWB);
+                const bool pad = C::KTAIL && kc == C::NK32 - 1;
+                const bf16x8_t kf = *reinterpret_cast<const bf16x8_t*>(
+                    smem + sbase + (pad ? kofft[C::KTAIL ? ks : 0] : koff[kc] + ks * 16 * C::ROWB));
 #pragma unroll
                 for (int qb = 0; qb < 2; ++qb) sacc[qb][ks] = mfma32(kf, qf[qb][kc], sacc[qb][ks]);
-            }
-            if constexpr (C::K16) {
-                const bf16x4_t kf = *reinterpret_cast<const bf16x4_t*>(smem + sbase + koff16 + ks * 16 * C::ROWB);
-#pragma unroll
-                for (int qb = 0; qb < 2; ++qb) sacc[qb][ks] = mfma16(kf, qf16[qb], sacc[qb][ks]);
             }
         }
         if (tail) {
@@ -421,31 +449,45 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
         }
     };
     // online softmax in place: sacc becomes the weights; running maxima and accumulators updated
-    auto softmax = [&](f32x4_t (&sacc)[2][4]) {
+    auto softmax = [&](f32x4_t (&sacc)[2][4], bool first) {
+        // Rescale only when some score exceeds its query's running maximum by
+        // more than 8 in the exp2 domain: below that the stale maximum
+        // keeps the weights <= 256, exact in bf16 and fp32 alike, and numerator
+        // and denominator share it. This keeps the row reductions and the
+        // accumulators out of VALU work on almost every tile.
+        float mx[2];
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
-            float mx = -INFINITY;
+            mx[qb] = fmaxf(fmaxf(sacc[qb][0][0], sacc[qb][0][1]), sacc[qb][0][2]);
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-                mx = fmaxf(fmaxf(mx, fmaxf(sacc[qb][ks][0], sacc[qb][ks][1])), fmaxf(sacc[qb][ks][2], sacc[qb][ks][3]));
-            mx = rows_max(mx);
-            // Rescale only when some query's maximum grew by more than 2^8 (in the
-            // exp2 domain): below that the stale maximum keeps the weights <= 256,
-            // exact in bf16 and fp32 alike, and numerator and denominator share it.
-            // This keeps the accumulators out of VALU work on almost every tile.
-            const float m_new = fmaxf(m_run[qb], mx);
-            if (__any((m_new - m_run[qb]) * cs > kRescaleLog2)) {
-                const float corr = fast_exp2((m_run[qb] - m_new) * cs);
-#pragma unroll
-                for (int h = 0; h < C::NHS; ++h) oacc[qb][h] *= corr;
-                m_run[qb] = m_new;
-            }
-            const float mc = m_run[qb] * cs;
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sacc[qb][ks][r] = fast_exp2(fmaf(sacc[qb][ks][r], cs, -mc));
+            for (int i = 3; i < 15; i += 2)
+                mx[qb] = fmaxf(fmaxf(mx[qb], sacc[qb][i / 4][i % 4]), sacc[qb][(i + 1) / 4][(i + 1) % 4]);
+            mx[qb] = fmaxf(mx[qb], sacc[qb][3][3]);
         }
+        if (first || __any(fmaxf(mx[0], mx[1]) > rescale_at)) {
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+                const float rm = rows_max(mx[qb]);
+                const float up = first ? rm : fmaxf(rm, 0.f);
+                if (!first) {
+                    const float corr = fast_exp2(-up * cs);
+#pragma unroll
+                    for (int h = 0; h < C::NHS; ++h) oacc[qb][h] *= corr;
+                }
+                m_run[qb] += up;
+                negm[qb] = f32x4_t{-m_run[qb], -m_run[qb], -m_run[qb], -m_run[qb]};
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sacc[qb][ks][r] -= up;
+            }
+        }
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sacc[qb][ks][r] = fast_exp2(sacc[qb][ks][r] * cs);
     };
     // O^T += V^T P^T for one tile
     auto pv = [&](uint32_t sbase, f32x4_t (&sacc)[2][4]) {
@@ -500,48 +542,49 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
         for (int qb = 0; qb < 2; ++qb) {
 #pragma unroll
             for (int kc = 0; kc < C::NK32; ++kc) asm volatile("" : "+v"(qf[qb][kc]));
-            if constexpr (C::K16) asm volatile("" : "+v"(qf16[qb]));
         }
     };
     f32x4_t sa[2][4];
-    // S-stage pipeline: step t reads stage t % S; tiles t + 1 .. t + S - 2 stay in flight
-    for (int t = 0; t < S - 1; ++t)
-        if (t < nt) issue(kt0 + t, t);
+    const bool active = row0 + wave * 32 < row_end;
+    // two stages: step t reads stage t % 2 while tile t + 1 loads into the other
+    if (nt > 0) issue(kt0, 0);
     fence_q();
     for (int t = 0; t < nt; ++t) {
-        if (t + S - 1 <= nt) wait_vmcnt<(S - 2) * C::IPW_MIN>();
-        else wait_vmcnt<0>();
+        wait_all();   // tile t has landed, and this wave's reads of the stage refilled below are done
         barrier_only();
-        if (t + S - 1 < nt) issue(kt0 + t + S - 1, (t + S - 1) % S);
+        if (t + 1 < nt) issue(kt0 + t + 1, (t + 1) % S);
         const int kt = kt0 + t;
+        if (!active) continue;   // every row of this wave lies past the segment: it only copies
         qk((t % S) * C::STAGEB, kt * kKeyTile, kt >= kfull, sa);
-        softmax(sa);
+        softmax(sa, t == 0);
         pv((t % S) * C::STAGEB, sa);
     }
 
-    // Output (or this key range's partial) through LDS: a lane holds 4
-    // consecutive head_dim values of one query row per 16 x 16 block, so
-    // direct stores write 8-byte pieces of 16 rows; staged in the (now free)
-    // stage memory, each wave writes its 32 rows as row-contiguous 16-byte
-    // vectors. Rows of 128 / 256 bytes XOR-swizzle their 16-byte chunks by
-    // the row (head_dim 72 rows are not swizzled).
+    // Output (or this key range's partial, in float32) through LDS: a lane
+    // holds 4 consecutive head_dim values of one query row per 16 x 16 block, so
+    // direct stores write 8- or 16-byte pieces of 16 rows; staged in the (now
+    // free) stage memory, each wave writes its 32 rows as row-contiguous 16-byte
+    // vectors. Rows of 128 / 256 bytes (float32: of a power of two) XOR-swizzle
+    // their 16-byte chunks by the row.
     constexpr int CH = HD / 8;                     // 16-byte chunks per row
+    constexpr int CF = HD / 4;                     // the same of a float32 row
     constexpr int SWM = C::SWZ ? (CH >= 16 ? 15 : CH - 1) : 0;
+    constexpr int SWF = (CF & (CF - 1)) == 0 ? (CF >= 16 ? 15 : CF - 1) : 0;
     __syncthreads();   // every wave is past its last read of the stages
-    uint8_t* const so = smem + wave * 32 * C::ROWB;
+    uint8_t* const so = smem + wave * 32 * C::ROWB * (a.nsplit == 1 ? 1 : 2);
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
         float l;
         if constexpr (C::SUM_IN_PAD) {
-            // rows 72..79 of subtile 4 are the ones rows: lane groups 2-3 hold them
+            // the last 8 rows of the last subtile are the ones rows: lane groups 2-3 hold them
             const float t0 = grp >= 2 ? oacc[qb][C::NHS - 1][0] : 0.f;
             auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(t0), __float_as_uint(t0), false, false);
             l = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
         } else {
             l = oacc[qb][C::NHS - 1][0];
         }
-        // normalised by this key range's own sum (bf16 holds it to the
-        // output's precision at half the bytes of float32)
+        // normalised by this key range's own sum; bf16 rows of the output, or
+        // float32 rows of the partial
         const float inv_l = 1.0f / l;
         const int rl = qb * 16 + l16;
 #pragma unroll
@@ -551,7 +594,10 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
                 float v[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) v[r] = oacc[qb][h][r] * inv_l;
-                store4<bf16_t>(reinterpret_cast<bf16_t*>(so + rl * C::ROWB + (((cidx / 8) ^ (rl & SWM)) * 16) + (cidx % 8) * 2), v);
+                if (a.nsplit == 1)
+                    store4<bf16_t>(reinterpret_cast<bf16_t*>(so + rl * C::ROWB + (((cidx / 8) ^ (rl & SWM)) * 16) + (cidx % 8) * 2), v);
+                else
+                    store4<float>(reinterpret_cast<float*>(so + rl * 2 * C::ROWB) + ((cidx / 4) ^ (rl & SWF)) * 4, v);
             }
         }
         const int qrow = row0 + wave * 32 + rl;
@@ -560,61 +606,69 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
                 make_float2(m_run[qb], l);
     }
     __syncthreads();
-    bf16_t* const dst = a.nsplit == 1 ? static_cast<bf16_t*>(a.o) : a.part_o + (long)split * a.M * d;
-#pragma unroll
-    for (int k = lane; k < 32 * CH; k += kWave) {
-        const int rl = k / CH, c = k % CH;
-        const int qrow = row0 + wave * 32 + rl;
-        if (qrow < row_end)
-            st16(dst + (long)qrow * d + head * HD + c * 8, ld16(so + rl * C::ROWB + ((c ^ (rl & SWM)) * 16)));
+    if (a.nsplit == 1) {
+        bf16_t* const dst = static_cast<bf16_t*>(a.o);
+        for (int k = lane; k < 32 * CH; k += kWave) {
+            const int rl = k / CH, c = k % CH;
+            const int qrow = row0 + wave * 32 + rl;
+            if (qrow < row_end)
+                st16(dst + (long)qrow * d + head * HD + c * 8, ld16(so + rl * C::ROWB + ((c ^ (rl & SWM)) * 16)));
+        }
+    } else {
+        float* const dst = a.part_o + (long)split * a.M * d;
+        for (int k = lane; k < 32 * CF; k += kWave) {
+            const int rl = k / CF, c = k % CF;
+            const int qrow = row0 + wave * 32 + rl;
+            if (qrow < row_end)
+                st16(dst + (long)qrow * d + head * HD + c * 4, ld16(so + rl * 2 * C::ROWB + ((c ^ (rl & SWF)) * 16)));
+        }
     }
 }
 
 // Combine of the key-range partials, fixed split order: range s, with running
-// max m_s, sum l_s and normalised output O_s, has weight l_s 2^((m_s - m) c)
-// (m the largest m_s, c the log2-domain scale), and the output is the
-// weighted mean of the O_s. One thread per 8 columns of a row (16-byte
-// vectors); with the split count NS known at compile time every partial of
-// the thread is loaded before the first is used (NS = 0: any count, loaded
-// in turn). The arithmetic and its order do not depend on NS.
+// max m_s (exp2 domain), sum l_s and normalised output O_s, has weight
+// l_s 2^((m_s - m) c) (m the largest m_s, c the log2-domain scale), and the output is the weighted mean of
+// the O_s. One thread per 4 columns of a row (16-byte vectors); with the
+// split count NS known at compile time every partial of the thread is loaded
+// before the first is used (NS = 0: any count, in chunks of 8). The arithmetic
+// and its order do not depend on NS.
 template <int NS>
 __global__ __launch_bounds__(256) void attention_combine_kernel(AttnDesc a) {
-    const long n8 = (long)a.M * a.d / 8;
+    const long n4 = (long)a.M * a.d / 4;
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n8) return;
-    const long m = i / (a.d / 8);
-    const int col = (int)(i - m * (a.d / 8)) * 8;
+    if (i >= n4) return;
+    const long m = i / (a.d / 4);
+    const int col = (int)(i - m * (a.d / 4)) * 4;
     const int head = col / a.hd;
     const int ns = NS > 0 ? NS : a.nsplit;
     auto ml_of = [&](int s) { return a.part_ml + 2 * (((long)s * a.M + m) * a.n_heads + head); };
     auto po_of = [&](int s) { return a.part_o + ((long)s * a.M + m) * a.d + col; };
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
     float L = 0.f;
-    if constexpr (NS > 0) {
-        float2 ml[NS];
-        vec16 po[NS];
+    auto add = [&](float2 ml, float gmax, float4 po) {
+        const float w = fast_exp2((ml.x - gmax) * a.scale_log2) * ml.y;
+        L += w;
+        acc[0] += w * po.x; acc[1] += w * po.y; acc[2] += w * po.z; acc[3] += w * po.w;
+    };
+    constexpr int CH = NS > 0 ? NS : 8;
+    float gmax = -INFINITY;
+    float2 ml[CH];
+    float4 po[CH];
+    auto load = [&](int s0) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            ml[s] = *reinterpret_cast<const float2*>(ml_of(s));
-            po[s] = ld16(po_of(s));
-        }
-        float gmax = -INFINITY;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) gmax = fmaxf(gmax, ml[s].x);
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const float w = fast_exp2((ml[s].x - gmax) * a.scale_log2) * ml[s].y;
-            L += w;
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const uint32_t u = po[s].w[r >> 1];
-                acc[r] += w * __uint_as_float((r & 1) ? (u & 0xffff0000u) : (u << 16));
+        for (int j = 0; j < CH; ++j)
+            if (NS > 0 || s0 + j < ns) {
+                ml[j] = *reinterpret_cast<const float2*>(ml_of(s0 + j));
+                po[j] = *reinterpret_cast<const float4*>(po_of(s0 + j));
             }
-        }
+    };
+    if constexpr (NS > 0) {
+        load(0);
+#pragma unroll
+        for (int j = 0; j < CH; ++j) gmax = fmaxf(gmax, ml[j].x);
+#pragma unroll
+        for (int j = 0; j < CH; ++j) add(ml[j], gmax, po[j]);
     } else {
-        // any split count: chunks of 8 splits, each chunk's loads issued together
-        constexpr int CH = 8;
-        float gmax = -INFINITY;
         for (int s0 = 0; s0 < ns; s0 += CH) {
             float mv[CH];
 #pragma unroll
@@ -623,74 +677,68 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(AttnDesc a) {
             for (int j = 0; j < CH; ++j) gmax = fmaxf(gmax, mv[j]);
         }
         for (int s0 = 0; s0 < ns; s0 += CH) {
-            float2 ml[CH];
-            vec16 po[CH];
+            load(s0);
 #pragma unroll
-            for (int j = 0; j < CH; ++j) {
-                if (s0 + j < ns) {
-                    ml[j] = *reinterpret_cast<const float2*>(ml_of(s0 + j));
-                    po[j] = ld16(po_of(s0 + j));
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < CH; ++j) {
-                if (s0 + j >= ns) break;
-                const float w = fast_exp2((ml[j].x - gmax) * a.scale_log2) * ml[j].y;
-                L += w;
-#pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    const uint32_t u = po[j].w[r >> 1];
-                    acc[r] += w * __uint_as_float((r & 1) ? (u & 0xffff0000u) : (u << 16));
-                }
-            }
+            for (int j = 0; j < CH; ++j)
+                if (s0 + j < ns) add(ml[j], gmax, po[j]);
         }
     }
     const float inv = 1.0f / L;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) acc[r] *= inv;
-    bf16_t* o = static_cast<bf16_t*>(a.o) + m * a.d + col;
-    store4<bf16_t>(o, acc);
-    store4<bf16_t>(o + 4, acc + 4);
+    for (int r = 0; r < 4; ++r) acc[r] *= inv;
+    store4<bf16_t>(static_cast<bf16_t*>(a.o) + m * a.d + col, acc);
 }
 
 }  // namespace
 
-bool attention_fast_path(int dtype, int hd) {
-    return dtype == kBF16 && (hd == 64 || hd == 72 || hd == 128);
+// Split of the key range. Workgroups run in rounds of as many as the CUs hold
+// (set by the registers of each head_dim). Measured on MI355X over 1 to 24
+// ranges at head_dim 64, 72, 96 and 128: a round with k workgroups per CU takes
+// about 6 + 2.5 (k - 1) us to start and end plus, per 64-key tile, the tile's
+// MFMA count times 0.0115 + 0.0067 k us (12% more where an odd row length
+// leaves bank conflicts), and the combine a launch plus the partials' bytes at
+// ~6 TB/s. Against a fixed target of 640 workgroups the choice is 240 instead
+// of 528 at 205 rows of 12 heads over 4096 keys (attention and combine 20.0 ->
+// 16.1 us), 512 instead of 640 at 1024 rows of 16 heads of 72 (38.7 -> 36.0)
+// and no split at 16 requests of 10 to 60% of 1024 keys (26.2 -> 22.7).
+double attention_cost_us(int base, int nsplit, int tps, int hd, int M, int d) {
+    const int per_cu = hd <= 16 ? 5 : hd <= 48 ? 4 : hd <= 88 ? 3 : 2;
+    const int mfmas = 8 * ((hd + 31) / 32) + 4 * ((hd + 15) / 16 + (hd % 16 == 0));
+    const double unit = mfmas * (hd % 16 ? 1.12 : 1.0);
+    auto round_us = [&](long k) { return tps * unit * (0.0115 + 0.0067 * k) + 6.0 + 2.5 * (k - 1); };
+    const long groups = (long)base * nsplit, slots = 256L * per_cu, rest = groups % slots;
+    double us = (double)(groups / slots) * round_us(per_cu);
+    if (rest) us += round_us((rest + 255) / 256);
+    if (nsplit > 1) us += 2.5 + (4.0 * nsplit + 2) * M * d / 6.0e6;
+    return us;
 }
 
-// bf16, head_dim 64 / 72 / 128: the fast kernel (+ combine when split). Other
-// bf16 head_dims up to 128 and fp32 up to 64: the generic kernel.
+// bf16, head_dim a multiple of 8 up to 128: the direct-to-LDS kernel (its
+// partials combined below when the key range is split). fp32, head_dim up to
+// 64: the register-staged kernel.
 hipError_t launch_attention(int dtype, const AttnDesc& a, hipStream_t s) {
     if (a.M == 0) return hipSuccess;
-    if (attention_fast_path(dtype, a.hd)) {
-        dim3 grid(a.n_qtiles_fast * a.n_heads * a.nsplit), block(kThreads);
-        if (a.hd == 64) hipLaunchKernelGGL((attention_dma_kernel<64, 2>), grid, block, 0, s, a);
-        else if (a.hd == 72) hipLaunchKernelGGL((attention_dma_kernel<72, 2>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((attention_dma_kernel<128, 2>), grid, block, 0, s, a);
-        return hipGetLastError();
-    }
-    dim3 grid(a.n_qtiles, a.n_heads), block(kThreads);
+    dim3 block(kThreads);
     if (dtype == kBF16) {
-        if (a.hd <= 64)
-            hipLaunchKernelGGL((attention_kernel<bf16_t, 64>), grid, block, 0, s, a);
-        else if (a.hd <= 96)
-            hipLaunchKernelGGL((attention_kernel<bf16_t, 96>), grid, block, 0, s, a);
-        else if (a.hd <= 128)
-            hipLaunchKernelGGL((attention_kernel<bf16_t, 128>), grid, block, 0, s, a);
-        else
-            return hipErrorInvalidValue;
+        dim3 grid(a.n_qtiles_fast * a.n_heads * a.nsplit);
+        switch (a.hd) {
+#define MS_HD(n) case n: hipLaunchKernelGGL((attention_dma_kernel<n>), grid, block, 0, s, a); break;
+            MS_HD(8) MS_HD(16) MS_HD(24) MS_HD(32) MS_HD(40) MS_HD(48) MS_HD(56) MS_HD(64)
+            MS_HD(72) MS_HD(80) MS_HD(88) MS_HD(96) MS_HD(104) MS_HD(112) MS_HD(120) MS_HD(128)
+#undef MS_HD
+            default: return hipErrorInvalidValue;
+        }
     } else {
         if (a.hd > 64) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((attention_kernel<float, 64>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((attention_kernel<float, 64>), dim3(a.n_qtiles, a.n_heads), block, 0, s, a);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_attention_combine(int dtype, const AttnDesc& a, hipStream_t s) {
-    if (a.M == 0 || a.nsplit <= 1 || !attention_fast_path(dtype, a.hd)) return hipSuccess;
-    const long n8 = (long)a.M * a.d / 8;
-    const dim3 grid((unsigned)((n8 + 255) / 256)), block(256);
+    if (a.M == 0 || a.nsplit <= 1) return hipSuccess;
+    const long n4 = (long)a.M * a.d / 4;
+    const dim3 grid((unsigned)((n4 + 255) / 256)), block(256);
     switch (a.nsplit) {
         case 2: hipLaunchKernelGGL(attention_combine_kernel<2>, grid, block, 0, s, a); break;
         case 3: hipLaunchKernelGGL(attention_combine_kernel<3>, grid, block, 0, s, a); break;

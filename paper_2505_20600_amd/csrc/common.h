@@ -146,6 +146,10 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt(0x3f70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// s_waitcnt for every vector-memory and LDS access of the wave: before a
+// barrier after which other waves overwrite LDS that this one has read.
+__device__ __forceinline__ void wait_all() { __builtin_amdgcn_s_waitcnt(0x0070); }
+
 // Workgroup barrier without the memory fence of __syncthreads (callers order
 // their own memory operations with explicit waits).
 // The empty asm statements keep the compiler from moving memory accesses

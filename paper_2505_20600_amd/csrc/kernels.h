@@ -101,19 +101,20 @@ struct AttnDesc {
     float scale_log2;     // log2(e) / sqrt(hd)
     // bf16 path: 128-row query tiles, keys split over `nsplit` workgroups of
     // `tiles_per_split` 64-key tiles; partials (O normalised by its own key
-    // range's sum, in bf16, and that range's running max and sum) go to
+    // range's sum, and that range's running max and sum, all float32) go to
     // part_o [nsplit][M][d] / part_ml [nsplit][M][n_heads].
     int M, n_qtiles_fast, nsplit, tiles_per_split;
-    uint16_t* part_o;     // bf16
+    float* part_o;
     float* part_ml;
 };
-
-// True when launch_attention uses the bf16 fast kernel for this head_dim.
-bool attention_fast_path(int dtype, int hd);
 
 // a6: attention of the packed masked queries over every key of their request
 // (when the key range is split, the partials are left for launch_attention_combine).
 hipError_t launch_attention(int dtype, const AttnDesc& a, hipStream_t s);
+
+// Modelled time of the bf16 attention and its combine for `base` query tiles x
+// heads, their keys in `nsplit` ranges of `tps` 64-key tiles.
+double attention_cost_us(int base, int nsplit, int tps, int hd, int M, int d);
 
 // Combine of the key-range partials (no-op when nsplit == 1).
 hipError_t launch_attention_combine(int dtype, const AttnDesc& a, hipStream_t s);

@@ -66,16 +66,23 @@ struct Layout {
     size_t rows_d, inv_d, seg_start_d, seg_req_d, cu_tiles_d;    // every-token packing
     size_t ones;                                                 // all-ones mask [B][N]
     size_t u_src, u_tok;                                         // unmasked image rows (Y caching)
-    size_t xm, a, q, o, h, u, kv_dense, part_o, part_ml, gemm_part, total;
+    size_t xm, a, q, o, h, u, kv_dense, part_ml, gemm_part, total;
 };
 
-// Attention key-range split: enough workgroups to give every CU two to three,
-// bounded by the partial buffers (split count x rows <= attn_part_rows).
-constexpr int kAttnTargetGroups = 640;
-
+// Attention key-range split: bounded by the partial buffers (split count x
+// rows: the sums and maxima hold attn_part_rows, the float32 outputs
+// attn_part_o_rows).
 size_t attn_part_rows(const ms_model_desc& d, int32_t B) {
     const size_t BT = (size_t)B * ((size_t)d.n_text + (size_t)d.grid_h * d.grid_w);
     return std::max(BT, (size_t)(131072 / d.n_heads));
+}
+
+// The partial outputs lie over the MLP's hidden rows, which are dead until the
+// block's MLP, and the bytes reserved behind them.
+size_t attn_part_o_bytes(const ms_model_desc& d, int32_t B) { return attn_part_rows(d, B) * d.d_model * 2; }
+size_t attn_part_o_rows(const ms_model_desc& d, int32_t B) {
+    const size_t BT = (size_t)B * ((size_t)d.n_text + (size_t)d.grid_h * d.grid_w);
+    return (BT * d.mlp_mult * d.d_model * 2 + attn_part_o_bytes(d, B)) / ((size_t)d.d_model * 4);
 }
 
 int elt_bytes(int32_t dtype) { return dtype == MS_BF16 ? 2 : 4; }
@@ -132,9 +139,8 @@ Layout make_layout(const ms_model_desc& d, int32_t B) {
     L.q = take(BT * dm * e);
     L.o = take(BT * dm * e);
     L.h = take(BT * dm * e);
-    L.u = take(BT * f * e);
+    L.u = take(BT * f * e + attn_part_o_bytes(d, B));
     L.kv_dense = take(BT * 2 * dm * e);
-    L.part_o = take(attn_part_rows(d, B) * dm * 2);   // bf16
     L.part_ml = take(attn_part_rows(d, B) * (size_t)d.n_heads * 2 * 4);
     L.gemm_part = take(ms::gemm_part_floats(dm) * 4);
     L.total = off;
@@ -347,11 +353,21 @@ void finish_packing(Packing& p, const ms_model_desc& desc, int batch, int T, int
     }
     const int ntiles = (T + 63) / 64;
     const int base = std::max(1, p.n_qtiles_fast * desc.n_heads);
-    int target = kAttnTargetGroups;
-    if (const char* ev = std::getenv("MS_ATTN_SPLIT_TARGET")) target = std::max(1, std::atoi(ev));
-    int ns = std::min(ntiles, std::max(1, (target + base - 1) / base));
-    if (p.M > 0) ns = std::min(ns, std::max(1, (int)(attn_part_rows(desc, batch) / p.M)));
-    if (!ms::attention_fast_path(desc.dtype, hd)) ns = 1;
+    const size_t part_rows = std::min(attn_part_rows(desc, batch), attn_part_o_rows(desc, batch));
+    const int most = p.M > 0 && desc.dtype == MS_BF16 ? std::max(1, std::min(ntiles, (int)(part_rows / p.M))) : 1;
+    int ns = 1;
+    if (const char* ev = std::getenv("MS_ATTN_SPLIT_TARGET")) {   // tuning knob: workgroups to reach
+        ns = std::min(most, std::max(1, (std::max(1, std::atoi(ev)) + base - 1) / base));
+    } else {
+        double best = 1e30;
+        for (int k = 1; k <= most; ++k) {
+            const double us = ms::attention_cost_us(base, k, (ntiles + k - 1) / k, hd, p.M, desc.d_model);
+            if (us < best) {
+                best = us;
+                ns = k;
+            }
+        }
+    }
     const int tps = (ntiles + ns - 1) / ns;
     p.attn_tps = tps;
     p.attn_nsplit = (ntiles + tps - 1) / tps;
@@ -524,7 +540,7 @@ ms_status block_forward(ms_step* s, const Packing& pk, const ms_layer_weights* w
     ad.n_qtiles_fast = pk.n_qtiles_fast;
     ad.nsplit = pk.attn_nsplit;
     ad.tiles_per_split = pk.attn_tps;
-    ad.part_o = static_cast<uint16_t*>(s->buf(s->lay.part_o));
+    ad.part_o = static_cast<float*>(s->buf(s->lay.u));
     ad.part_ml = static_cast<float*>(s->buf(s->lay.part_ml));
     {
         ProfScope p(MS_K_ATTENTION, st);
