@@ -7,16 +7,17 @@
 // [N][K]), the native operand layout of the CDNA4 matrix cores. The weight
 // tile is the MFMA "A" operand and the activation tile the "B" operand, so
 // each lane ends up with four consecutive output columns of one row; the
-// QKV and plain-bias epilogues and the split-K partials first restage the
-// tile through LDS so that consecutive lanes write consecutive columns.
+// tile is restaged through LDS so that consecutive lanes write consecutive
+// columns.
 //
 // Epilogues: bias; bias + residual (out-projection and MLP-down); bias +
-// erf-GELU (MLP-up, erf to 5.5e-7); QKV, which writes Q to its own buffer
+// GELU (MLP-up, to 3.3e-7); QKV, which writes Q to its own buffer
 // and the fresh K/V of each masked token straight into that token's row of
 // the working K/V (the K/V cache of Fig. 7 with the masked rows replaced).
 //
 // bf16 tiles: BM x BN from 64 x 64 to 256 x 256, operands copied global ->
-// LDS without staging registers into 2-4 stages of 64-deep K steps; fp32:
+// LDS without staging registers into 2-4 stages of 64-deep K steps, the 256 x
+// 256 and 256 x 192 ones refilled region by region (gemm_pp_kernel); fp32:
 // 64 x 64 tiles through registers, double-buffered. The host picks tile,
 // stage count and K split from a step-time table measured on MI355X; split
 // workgroups write float32 partials, summed in a fixed order by a second
@@ -27,6 +28,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -37,48 +39,176 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kCUs = 256;
 
-// erf(x) by Abramowitz & Stegun, Handbook of Mathematical Functions, formula
-// 7.1.26: 1 - t (a1 + t (a2 + t (a3 + t (a4 + t a5)))) exp(-x^2), t = 1 / (1 + p|x|),
-// odd in x; |error| <= 1.5e-7 (5.5e-7 evaluated in float32), far below the bf16
-// rounding of the GELU output, at one reciprocal, one exponential and five FMAs.
-__device__ __forceinline__ float erf_as(float x) {
+// GELU(x) = x (1 + erf(x / sqrt 2)) / 2 = max(x, 0) - |x| erfc(|x| / sqrt 2) / 2, with
+// erfc(y) by Abramowitz & Stegun, Handbook of Mathematical Functions, formula
+// 7.1.26: t (a1 + t (a2 + t (a3 + t (a4 + t a5)))) exp(-y^2), t = 1 / (1 + p y),
+// |error| <= 1.5e-7, far below the bf16 rounding of the output; the tail of
+// negative x keeps its relative precision. One reciprocal, one exponential and
+// eleven other instructions (the epilogue of a 256 x 256 tile evaluates 128 per
+// lane, ~60 cycles each as 0.5 x (1 + erf)).
+__device__ __forceinline__ float gelu(float x) {
     const float ax = fabsf(x);
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, ax, 1.0f));
-    float poly = fmaf(1.061405429f, t, -1.453152027f);
-    poly = fmaf(poly, t, 1.421413741f);
-    poly = fmaf(poly, t, -0.284496736f);
-    poly = fmaf(poly, t, 0.254829592f);
-    poly *= t;
-    const float e = __builtin_amdgcn_exp2f(-(ax * ax) * 1.4426950408889634f);
-    return copysignf(fmaf(-poly, e, 1.0f), x);
+    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, ax, 1.0f));
+    float q = fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
+    q = fmaf(q, t, 0.5f * 1.421413741f);
+    q = fmaf(q, t, 0.5f * -0.284496736f);
+    q = fmaf(q, t, 0.5f * 0.254829592f);
+    q *= t * __builtin_amdgcn_exp2f(x * (x * (-0.5f * 1.4426950408889634f)));
+    return fmaf(-ax, q, fmaxf(x, 0.f));
+}
+
+// v + bias, and GELU where the epilogue has it.
+template <int EPI>
+__device__ __forceinline__ void epilogue_math(float v[4], const float bv[4]) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] += bv[r];
+    if constexpr (EPI == kEpiBiasGelu) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = gelu(v[r]);
+    }
+}
+
+// Where output columns n.. of packed row m go (kEpiQKV: a group of columns that
+// starts below g.d ends there, d and n being multiples of the group).
+template <int EPI, typename T = bf16_t>
+__device__ __forceinline__ T* epilogue_dst(const GemmDesc& g, int m, int n) {
+    if (EPI == kEpiQKV && n >= g.d) return static_cast<T*>(g.kv) + (long)g.rows[m] * g.kvld + (n - g.d);
+    return static_cast<T*>(g.C) + (long)m * g.ldc + n;
 }
 
 template <typename T, int EPI>
 __device__ __forceinline__ void epilogue_store(const GemmDesc& g, int m, int n, float v[4]) {
-    const T* __restrict__ bias = static_cast<const T*>(g.bias);
     float bv[4];
-    load4<T>(bias + n, bv);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] += bv[r];
+    load4<T>(static_cast<const T*>(g.bias) + n, bv);
+    epilogue_math<EPI>(v, bv);
     if constexpr (epi_resid(EPI)) {
         float rv[4];
         load4<T>(static_cast<const T*>(g.R) + (long)m * g.ldr + n, rv);
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] += rv[r];
     }
-    if constexpr (EPI == kEpiBiasGelu) {
+    store4<T>(epilogue_dst<EPI, T>(g, m, n), v);
+}
+
+// Epilogue of an unsplit, residual-free tile of the eight- or four-wave kernels
+// (two waves along m, WN along n; SM x SN 16 x 16 blocks each): run on the
+// registers, staged in LDS as bf16 (16-byte chunks XOR-swizzled by the row) and
+// stored row by row, 16 bytes per lane: an MFMA block leaves a lane 4 columns of
+// one row, so direct stores write 32-byte pieces of 16 rows. Against staging the
+// float32 tile, in two passes where it does not fit: 8547x3456x1152 (256x256
+// tiles, bias) 77.4 -> 67.8 us, 8547x4608x1152 (GELU) 127.3 -> 118.2 us.
+// Starts and ends with the workgroup past its last LDS read.
+template <int EPI, int BM, int BN, int WN, int SM, int SN>
+__device__ __forceinline__ void store_tile_bf16(const GemmDesc& g, void* smem, const f32x4_t (&acc)[SN][SM], int m0, int n0,
+                                                int tid, int wm, int wn) {
+    constexpr int CPR = BN / 8, THREADS = 2 * WN * kWave;
+    const int l16 = tid % 16, grp = tid % kWave / 16;
+    bf16_t* const sb = static_cast<bf16_t*>(smem);
+    __syncthreads();
 #pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = 0.5f * v[r] * (1.0f + erf_as(v[r] * 0.70710678118654752f));
-    }
-    if constexpr (EPI == kEpiQKV) {
-        if (n < g.d) {
-            store4<T>(static_cast<T*>(g.C) + (long)m * g.ldc + n, v);
-        } else {
-            const long tok = g.rows[m];
-            store4<T>(static_cast<T*>(g.kv) + tok * g.kvld + (n - g.d), v);
+    for (int i = 0; i < SN; ++i) {
+        const int nl = wn * (BN / WN) + i * 16 + grp * 4;
+        float bv[4];
+        load4<bf16_t>(static_cast<const bf16_t*>(g.bias) + min(n0 + nl, g.N - 4), bv);
+#pragma unroll
+        for (int j = 0; j < SM; ++j) {
+            const int ml = wm * (BM / 2) + j * 16 + l16;
+            float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+            epilogue_math<EPI>(v, bv);
+            store4<bf16_t>(sb + ml * BN + (((nl / 8) ^ (ml & 7)) * 8) + nl % 8, v);
         }
-    } else {
-        store4<T>(static_cast<T*>(g.C) + (long)m * g.ldc + n, v);
+    }
+    __syncthreads();
+    const bool wide = g.ldc % 8 == 0 && (EPI != kEpiQKV || g.kvld % 8 == 0);   // 16-byte aligned rows
+    for (int idx = tid; idx < BM * CPR; idx += THREADS) {
+        const int ml = idx / CPR, c = idx % CPR;
+        const int m = m0 + ml, n = n0 + c * 8;
+        if (m >= g.M || n >= g.N) continue;
+        const vec16 t = ld16(sb + ml * BN + ((c ^ (ml & 7)) * 8));
+        bf16_t* const o = epilogue_dst<EPI>(g, m, n);
+        if (wide && n + 8 <= g.N) {
+            st16(o, t);
+        } else {   // N is a multiple of 4
+            *reinterpret_cast<uint2*>(o) = make_uint2(t.w[0], t.w[1]);
+            if (n + 4 < g.N) *reinterpret_cast<uint2*>(o + 4) = make_uint2(t.w[2], t.w[3]);
+        }
+    }
+    __syncthreads();
+}
+
+// Residual outputs and split-K partials: the float32 tile is staged in PASSES
+// passes (16-byte chunks XOR-swizzled by the row), each wave row's blocks spread
+// evenly over them; a lane then takes 8 columns of a row (16-byte residual loads
+// and stores; 8547x1152x1152 34.6 -> 34.1 us against 4 columns), of a partial 4
+// (32 bytes per lane: 1434x768x3072 in four ranges 18.2 -> 19.2 us). Starts and ends with the workgroup past its last LDS read.
+template <int EPI, int BM, int BN, int WN, int SM, int SN, int PASSES>
+__device__ __forceinline__ void store_tile_f32(const GemmDesc& g, void* smem, const f32x4_t (&acc)[SN][SM], int m0, int n0,
+                                               int kz, int tid, int wm, int wn) {
+    static_assert(SM % PASSES == 0, "passes");
+    constexpr int CPR = BN / 8, THREADS = 2 * WN * kWave, JP = SM / PASSES, RW = JP * 16;   // rows of a wave row per pass
+    const int l16 = tid % 16, grp = tid % kWave / 16;
+    float* const sc = static_cast<float*>(smem);
+    const bool wide = g.ldc % 8 == 0 && (!epi_resid(EPI) || g.ldr % 8 == 0) && (EPI != kEpiQKV || g.kvld % 8 == 0);
+    __syncthreads();
+#pragma unroll
+    for (int pass = 0; pass < PASSES; ++pass) {
+#pragma unroll
+        for (int i = 0; i < SN; ++i) {
+            const int nl = wn * (BN / WN) + i * 16 + grp * 4;
+#pragma unroll
+            for (int j = 0; j < JP; ++j) {
+                const int ml = wm * RW + j * 16 + l16;
+                const f32x4_t& a = acc[i][pass * JP + j];
+                *reinterpret_cast<float4*>(sc + ml * BN + (((nl / 4) ^ (ml & 15)) * 4)) = make_float4(a[0], a[1], a[2], a[3]);
+            }
+        }
+        __syncthreads();
+        if (g.ksplit > 1) {
+            constexpr int CPF = BN / 4;
+            for (int idx = tid; idx < 2 * RW * CPF; idx += THREADS) {
+                const int ml = idx / CPF, c = idx % CPF;
+                const int m = m0 + (ml / RW) * (BM / 2) + pass * RW + ml % RW, n = n0 + c * 4;
+                if (m < g.M && n < g.N)
+                    st16(g.part + ((long)kz * g.M + m) * g.N + n, ld16(sc + ml * BN + ((c ^ (ml & 15)) * 4)));
+            }
+            __syncthreads();
+            continue;
+        }
+        for (int idx = tid; idx < 2 * RW * CPR; idx += THREADS) {
+            const int ml = idx / CPR, c = idx % CPR;
+            const int m = m0 + (ml / RW) * (BM / 2) + pass * RW + ml % RW, n = n0 + c * 8;
+            if (m >= g.M || n >= g.N) continue;
+            float v[8];
+            load4<float>(sc + ml * BN + (((2 * c) ^ (ml & 15)) * 4), v);
+            load4<float>(sc + ml * BN + (((2 * c + 1) ^ (ml & 15)) * 4), v + 4);
+            if (wide && n + 8 <= g.N) {
+                const vec16 bw = ld16(static_cast<const bf16_t*>(g.bias) + n);
+                vec16 rw = {{0u, 0u, 0u, 0u}}, ow;
+                if constexpr (epi_resid(EPI)) rw = ld16(static_cast<const bf16_t*>(g.R) + (long)m * g.ldr + n);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    float bv[4], rv[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const uint32_t wb = bw.w[2 * h + r / 2], wr = rw.w[2 * h + r / 2];
+                        bv[r] = __uint_as_float(r & 1 ? wb & 0xffff0000u : wb << 16);
+                        rv[r] = __uint_as_float(r & 1 ? wr & 0xffff0000u : wr << 16);
+                    }
+                    epilogue_math<EPI>(v + 4 * h, bv);
+                    if constexpr (epi_resid(EPI)) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) v[4 * h + r] += rv[r];
+                    }
+                    ow.w[2 * h] = pack_bf16x2(v[4 * h], v[4 * h + 1]);
+                    ow.w[2 * h + 1] = pack_bf16x2(v[4 * h + 2], v[4 * h + 3]);
+                }
+                st16(epilogue_dst<EPI>(g, m, n), ow);
+            } else {
+                epilogue_store<bf16_t, EPI>(g, m, n, v);
+                if (n + 4 < g.N) epilogue_store<bf16_t, EPI>(g, m, n + 4, v + 4);
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -229,12 +359,11 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(GemmDesc g) {
 // that sees them must assume each may write the stage being read and drains
 // every load in flight before the first fragment read of each step.
 
-// Waves per workgroup of the direct-to-LDS kernel: 256x256, 256x192 and
-// 192x192 tiles run eight waves (2 x 4, 128 x 64, 128 x 48 or 96 x 48
-// outputs each), the other tiles four (2 x 2). 192-wide tiles fill the 256
-// CUs in whole waves where the projection widths are multiples of 192 and not
-// of 256 (1152, 3072, 4608, 12288 columns); 192x192 holds three stages in LDS
-// and quantises rows more finely than 256-row tiles.
+// Waves per workgroup of this kernel: 192x192 tiles run eight (2 x 4, 96 x 48
+// outputs each), the other tiles four (2 x 2). 192-wide tiles fill the 256 CUs
+// in whole waves where the projection widths are multiples of 192 and not of
+// 256 (1152, 3072, 4608, 12288 columns); 192x192 holds three stages in LDS and
+// quantises rows more finely than 256-row tiles.
 constexpr int dl_waves(int bm, int bn) { return bm * bn >= 192 * 192 ? 8 : 4; }
 
 template <int BM, int BN, int S, int EPI>
@@ -252,12 +381,11 @@ __global__ __launch_bounds__(kWave * dl_waves(BM, BN)) void gemm_dl_kernel(GemmD
     constexpr int SN = BN / WN / 16;            // 16-col MFMA blocks per wave (cols n)
     static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "load split");
     // S activation stages, then S weight stages; after the main loop the
-    // same LDS stages the output tile when its float32 form fits
+    // same LDS stages the output tile
     __shared__ __attribute__((aligned(1024))) bf16_t smem[S * (BM + BN) * ROWE];
     bf16_t* const sAb = smem;
     bf16_t* const sWb = smem + S * BM * ROWE;
-    // output staging passes: the float32 tile in one pass, or in two halves
-    // of its rows (the two wave rows) when only half fits
+    // passes that stage the float32 tile: one, or two when only half fits
     constexpr int kLdsBytes = S * (BM + BN) * ROWE * 2;
     constexpr int kOutPasses = kLdsBytes >= BM * BN * 4 ? 1 : 2;
     static_assert(kLdsBytes * 2 >= BM * BN * 4 && WM == 2, "output staging");
@@ -373,79 +501,192 @@ __global__ __launch_bounds__(kWave * dl_waves(BM, BN)) void gemm_dl_kernel(GemmD
         }
     }
 
-    // Output through LDS: an MFMA block leaves each lane 4 columns of 16 rows,
-    // so direct stores write 32-byte pieces of 16 rows; staged, consecutive
-    // lanes write consecutive 4-column groups of one row. Float32 in LDS, so
-    // the epilogue arithmetic is unchanged. The 16-byte chunks of a staged
-    // row are XOR-swizzled by (row & 15), so both the 16-row writes and the
-    // row-wise reads are conflict-free. Tiles too large for one pass stage
-    // the rows of one wave row (BM / 2) at a time.
-    // The host picks the path per launch (GemmDesc::direct_out): direct
-    // stores only for the GELU epilogue of launches with few tiles per CU.
     const int hw_next = hw + (int)gridDim.x;
-    const bool more = hw_next < total;
-    if (EPI == kEpiBiasGelu && g.direct_out) {
-        // direct stores from registers: the next tile's first stages load
-        // during them (every wave is past its last read of the stages)
-        const int cm0 = m0, cn0 = n0;
-        if (more) {
-            barrier_only();
-            setup(hw_next);
-            prologue();
-        }
-#pragma unroll
-        for (int i = 0; i < SN; ++i) {
-            const int n = cn0 + wn * (BN / WN) + i * 16 + grp * 4;
-            if (n >= N) continue;
-#pragma unroll
-            for (int j = 0; j < SM; ++j) {
-                const int m = cm0 + wm * (BM / WM) + j * 16 + lane % 16;
-                if (m >= M) continue;
-                float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
-                epilogue_store<bf16_t, EPI>(g, m, n, v);
-            }
-        }
-        if (!more) return;
-        hw = hw_next;
-        continue;
-    }
-    constexpr int CPR = BN / 4;               // 16-byte chunks per staged row
-    constexpr int PR = BM / kOutPasses;       // rows per pass
-    float* const sc = reinterpret_cast<float*>(smem);
-#pragma unroll
-    for (int pass = 0; pass < kOutPasses; ++pass) {
-        __syncthreads();   // operand reads (or the previous pass's reads) are done
-        if (kOutPasses == 1 || wm == pass) {
-#pragma unroll
-            for (int i = 0; i < SN; ++i) {
-                const int nl = wn * (BN / WN) + i * 16 + grp * 4;
-#pragma unroll
-                for (int j = 0; j < SM; ++j) {
-                    const int ml = wm * (BM / WM) + j * 16 + lane % 16 - pass * PR;
-                    *reinterpret_cast<float4*>(sc + ml * BN + (((nl / 4) ^ (ml & 15)) * 4)) =
-                        make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-                }
-            }
-        }
-        __syncthreads();
-        for (int idx = tid; idx < PR * CPR; idx += NW * kWave) {
-            const int ml = idx / CPR, c = idx % CPR;
-            const int m = m0 + pass * PR + ml, n = n0 + c * 4;
-            if (m >= M || n >= N) continue;
-            const float4 t = *reinterpret_cast<const float4*>(sc + ml * BN + ((c ^ (ml & 15)) * 4));
-            if (g.ksplit == 1) {
-                float v[4] = {t.x, t.y, t.z, t.w};
-                epilogue_store<bf16_t, EPI>(g, m, n, v);
-            } else {
-                *reinterpret_cast<float4*>(g.part + ((long)kz * M + m) * N + n) = t;
-            }
-        }
-    }
-    if (!more) return;
-    __syncthreads();   // the staging reads are done before the stages refill
+    if (!epi_resid(EPI) && g.ksplit == 1) store_tile_bf16<EPI, BM, BN, WN, SM, SN>(g, smem, acc, m0, n0, tid, wm, wn);
+    else store_tile_f32<EPI, BM, BN, WN, SM, SN, kOutPasses>(g, smem, acc, m0, n0, kz, tid, wm, wn);
+    if (hw_next >= total) return;
     hw = hw_next;
     setup(hw);
     prologue();
+    }
+}
+
+// The 256-row, eight-wave tiles (256 x 256 and 256 x 192; waves 2 x 4, 128 x 64
+// or 128 x 48 outputs each): the K step of 64 runs in four phases, each the
+// products of one quarter of a wave's rows (32) with all of its columns. Phase
+// q's MFMAs read registers only; meanwhile the next quarter's rows are read
+// from LDS, and in phase 3 each 16-column block of the weights is replaced by
+// the next step's as soon as its last product is issued.
+//
+// An LDS stage is refilled region by region (a quarter of the rows, or one
+// 16-column block of every wave: 8 KB, one copy per wave): a region's reads
+// are complete at the barrier after the phase that used them, so step k + 2's
+// weights are copied in phases 1 and 2 of step k, its rows in phases 3 and 0.
+// Every copy has four to six phases to land, and at each phase start the copies
+// issued after the one it needs may stay in flight (a fixed count per phase).
+// Copies past the last K step go through an empty buffer resource (zeros, no
+// traffic), so the counts hold to the end.
+//
+// Why: with a whole stage per K step, copied under the step before and waited
+// for at its end, the matrix cores stood idle 40-50% of the time; here the
+// operands of more than one step are in flight, and no MFMA waits for an LDS
+// read issued in its own phase. A step of 256 x 256 x 64 on every CU takes 1.5
+// us, against 1.1 without the copies, 1.3 without the LDS reads and 0.9 with the
+// MFMAs alone: what is left is the operand
+// stream from L2 (64 KB per CU and step) under the LDS reads. Against the
+// stage-per-step loop (bf16 outputs staged in both): 16384x3072x12288 1006 ->
+// 930 us, 3732x3072x12288 276 -> 235, 3732x12288x3072 273 -> 240, 12288x6144x3072
+// 407 -> 355, 4096^3 112 -> 105. One barrier per two phases, wave priorities
+// and four waves of 128 x 128 were even or slower (the last by 35%).
+template <int BN>
+struct PpCfg {
+    static constexpr int SN = BN / 64;                  // 16-column blocks per wave
+    static constexpr int kStage = (256 + BN) * 128;     // bytes
+    static constexpr int W0 = 256 * 128;                // regions of 8 KB: A0..A3, then the W blocks
+    // copies in flight at the start of phase 0..3: issued (order W, A0..A3 of a
+    // step) after the region the phase reads
+    static constexpr int V0 = 2 + SN + 2, V1 = 1 + SN + 4, V2 = SN + 4 + 2, V3 = 3 + SN;
+};
+
+template <int BN, int EPI>
+__global__ __launch_bounds__(512) void gemm_pp_kernel(GemmDesc g) {
+    using C = PpCfg<BN>;
+    using E = Elt<bf16_t>;
+    using frag_t = typename E::frag_t;
+    constexpr int BM = 256, SM = 8, SN = C::SN, NW = 8;
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * C::kStage];
+    const uint32_t lds0 = lds_addr(smem);
+
+    const int tid = threadIdx.x;
+    const int lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int wm = wave % 2, wn = wave / 2;
+    const int M = g.M, N = g.N, K = g.K;
+    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+    const int total = tiles_m * tiles_n * g.ksplit;
+    const bf16_t* __restrict__ A = static_cast<const bf16_t*>(g.A);
+    const bf16_t* __restrict__ W = static_cast<const bf16_t*>(g.W);
+
+    // A region's 64 rows: A quarter q has rows wm' 128 + q 32 + 0..31 of both
+    // wave rows, W block i columns wn' 16 SN + i 16 + 0..15 of the four wave
+    // columns. This wave copies rows 8 wave .. 8 wave + 7: this lane's byte
+    // offset inside the tile's operand (quarter and block are scalar offsets).
+    const int rr = wave * 8 + lane / 8;
+    const int chunk = (lane % 8) ^ ((rr >> 1) & 7);
+    const uint32_t va = (uint32_t)(((rr / 32) * 128 + rr % 32) * g.lda + chunk * 8) * 2u;
+    const uint32_t vw = (uint32_t)(((rr / 16) * 16 * SN + rr % 16) * K + chunk * 8) * 2u;
+    const uint32_t astep = (uint32_t)g.lda * 64u, wstep = (uint32_t)K * 32u;   // 32 rows, 16 columns
+
+    // LDS fragment addresses: row l16 of the wave's rows in a region, logical
+    // chunk ks * 4 + lane group
+    const int l16 = lane % 16, grp = lane / 16;
+    const uint32_t f0 = l16 * 128 + ((grp ^ (l16 >> 1)) * 16), f1 = l16 * 128 + (((4 + grp) ^ (l16 >> 1)) * 16);
+    const uint32_t pa[2] = {lds0 + wm * 4096 + f0, lds0 + wm * 4096 + f1};
+    const uint32_t pw[2] = {lds0 + C::W0 + wn * 2048 + f0, lds0 + C::W0 + wn * 2048 + f1};
+    typedef const __attribute__((address_space(3))) frag_t* lfrag;
+
+    int hw = blockIdx.x;
+    for (;;) {
+    const TileIdx ti = tile_of(xcd_logical_block(hw, total), tiles_m, tiles_n, BM, BN, g.group_m);
+    const int kz = ti.kz, m0 = ti.m0, n0 = ti.n0;
+    const int kbeg = kz * g.kchunk;
+    const int nk = (min(K, kbeg + g.kchunk) - kbeg) / 64;
+    u32x4_t rA = raw_rsrc(A + (size_t)m0 * g.lda, (uint32_t)((size_t)min(BM, M - m0) * g.lda * 2));
+    u32x4_t rW = raw_rsrc(W + (size_t)n0 * K, (uint32_t)((size_t)min(BN, N - n0) * K * 2));
+    const uint32_t bytesA = rA[2], bytesW = rW[2];
+    // region copies of K step kt into stage st = kt % 2; past the end through an empty resource
+    auto copy_a = [&](int st, int kt, int q) {
+        rA[2] = kt < nk ? bytesA : 0u;
+        dma_buf16(rA, va, (uint32_t)(kbeg + kt * 64) * 2u + q * astep, lds0 + st * C::kStage + q * 8192 + wave * 1024);
+    };
+    auto copy_w = [&](int st, int kt, int i) {
+        if (i >= SN) return;
+        rW[2] = kt < nk ? bytesW : 0u;
+        dma_buf16(rW, vw, (uint32_t)(kbeg + kt * 64) * 2u + i * wstep, lds0 + st * C::kStage + C::W0 + i * 8192 + wave * 1024);
+    };
+    auto read_a = [&](int st, int q, frag_t (&f)[2][2]) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            uint32_t b = pa[ks] + st * C::kStage;
+            asm volatile("" : "+v"(b));   // one address: region and block offsets fold into the reads
+#pragma unroll
+            for (int j = 0; j < 2; ++j) f[j][ks] = *(lfrag)(uintptr_t)(b + q * 8192 + j * 2048);
+        }
+    };
+    auto read_w = [&](int st, int i, frag_t (&f)[2]) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            uint32_t b = pw[ks] + st * C::kStage;
+            asm volatile("" : "+v"(b));
+            f[ks] = *(lfrag)(uintptr_t)(b + i * 8192);
+        }
+    };
+
+    f32x4_t acc[SN][SM];
+#pragma unroll
+    for (int i = 0; i < SN; ++i)
+#pragma unroll
+        for (int j = 0; j < SM; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    frag_t fa[2][2][2], fw[SN][2];   // two sets of a quarter's rows; the wave's columns
+
+    // phase q of K step kt (stage st)
+    auto phase = [&](auto stage, auto quarter, int kt) {
+        constexpr int st = decltype(stage)::value, q = decltype(quarter)::value;
+        constexpr int V = q == 0 ? C::V0 : q == 1 ? C::V1 : q == 2 ? C::V2 : C::V3;
+        __builtin_amdgcn_sched_barrier(0);
+        wait_vmcnt<V>();
+        barrier_only();
+#pragma unroll
+        for (int i = 0; i < SN; ++i) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][2 * q + j] = E::mma(fw[i][ks], fa[q & 1][j][ks], acc[i][2 * q + j]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i == 0) read_a(q == 3 ? st ^ 1 : st, (q + 1) & 3, fa[(q + 1) & 1]);
+            if (q == 3) read_w(st ^ 1, i, fw[i]);
+            if (i == 1) {
+                if (q == 0) { copy_a(st ^ 1, kt + 1, 2); copy_a(st ^ 1, kt + 1, 3); }
+                if (q == 1) { copy_w(st, kt + 2, 0); copy_w(st, kt + 2, 1); }
+                if (q == 2) { copy_w(st, kt + 2, 2); copy_w(st, kt + 2, 3); }
+                if (q == 3) { copy_a(st, kt + 2, 0); copy_a(st, kt + 2, 1); }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto kstep = [&](auto stage, int kt) {
+        phase(stage, std::integral_constant<int, 0>{}, kt);
+        phase(stage, std::integral_constant<int, 1>{}, kt);
+        phase(stage, std::integral_constant<int, 2>{}, kt);
+        phase(stage, std::integral_constant<int, 3>{}, kt);
+    };
+#pragma unroll
+    for (int i = 0; i < SN; ++i) copy_w(0, 0, i);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) copy_a(0, 0, q);
+#pragma unroll
+    for (int i = 0; i < SN; ++i) copy_w(1, 1, i);
+    copy_a(1, 1, 0);
+    copy_a(1, 1, 1);
+    wait_vmcnt<3 + SN + 2>();   // W and A0 of step 0
+    barrier_only();
+    read_a(0, 0, fa[0]);
+#pragma unroll
+    for (int i = 0; i < SN; ++i) read_w(0, i, fw[i]);
+    // in pairs of steps (the stages are compile-time constants); an odd last one
+    // multiplies the zeros of the empty copies
+    // (one loop exit: a second one made the compiler keep two copies of acc)
+    for (int kt = 0; kt < nk; kt += 2) {
+        kstep(std::integral_constant<int, 0>{}, kt);
+        kstep(std::integral_constant<int, 1>{}, kt + 1);
+    }
+    wait_all();   // the zero copies too: the stages take the output next
+
+    const int hw_next = hw + (int)gridDim.x;
+    if (!epi_resid(EPI) && g.ksplit == 1) store_tile_bf16<EPI, BM, BN, 4, SM, SN>(g, smem, acc, m0, n0, tid, wm, wn);
+    else store_tile_f32<EPI, BM, BN, 4, SM, SN, 2>(g, smem, acc, m0, n0, kz, tid, wm, wn);
+    if (hw_next >= total) return;
+    hw = hw_next;
     }
 }
 
@@ -507,6 +748,25 @@ hipError_t launch_dl_epi(const GemmDesc& g, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int BN, int EPI>
+hipError_t launch_pp_epi(const GemmDesc& g, hipStream_t s) {
+    const long tiles = (long)((g.N + BN - 1) / BN) * ((g.M + 255) / 256) * g.ksplit;
+    hipLaunchKernelGGL((gemm_pp_kernel<BN, EPI>), dim3(dl_grid(kCUs, tiles)), dim3(512), 0, s, g);
+    return hipGetLastError();
+}
+
+template <int BN>
+hipError_t launch_pp(const GemmDesc& g, hipStream_t s) {
+    switch (g.epilogue) {
+        case kEpiBias: return launch_pp_epi<BN, kEpiBias>(g, s);
+        case kEpiBiasResid: return launch_pp_epi<BN, kEpiBiasResid>(g, s);
+        case kEpiBiasGelu: return launch_pp_epi<BN, kEpiBiasGelu>(g, s);
+        case kEpiQKV: return launch_pp_epi<BN, kEpiQKV>(g, s);
+        case kEpiBiasResidMlp: return launch_pp_epi<BN, kEpiBiasResidMlp>(g, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 template <int BM, int BN, int S>
 hipError_t launch_dl(const GemmDesc& g, hipStream_t s) {
     switch (g.epilogue) {
@@ -543,10 +803,7 @@ hipError_t launch_reduce(const GemmDesc& g, hipStream_t s) {
 // from timing grids of n x 256 tiles (16 tile columns, GELU epilogue) at
 // K = 1024 and K = 4096 on MI355X with the direct-to-LDS main loop; between
 // the measured n the model interpolates linearly, past n = 48 it scales with n.
-// Checked against 17 projection shapes of the workloads (M 1243..16384,
-// N 1152..12288, K 768..12288): the predicted rate is within 10% of the
-// measured one for the chosen tile on all but the deepest K (12288, +26%,
-// same choice). Split-K multiplies the groups, divides the steps and adds the
+// Split-K multiplies the groups, divides the steps and adds the
 // partial-sum pass.
 namespace {
 constexpr int kCostN = 13;
@@ -557,42 +814,42 @@ struct TileCost {
     double tile[kCostN];   // b(n), us per launch
 };
 constexpr TileCost kCost[] = {
-    {256, 256, 2, {1.353, 2.677, 3.726, 5.789, 7.043, 9.378, 11.009, 12.507, 18.991, 24.576, 34.741, 49.206, 73.895},
-     {23.6, 44.1, 81.1, 79.3, 103.5, 98.8, 114.7, 172.7, 215.0, 360.7, 556.3, 541.7, 843.8}},
-    {256, 192, 2, {1.056, 2.152, 3.243, 4.544, 6.230, 7.835, 9.340, 10.339, 14.877, 19.229, 30.646, 39.311, 59.356},
-     {18.8, 29.5, 40.4, 47.4, 49.2, 51.8, 61.3, 82.1, 173.6, 237.3, 322.0, 447.8, 652.3}},
-    {192, 192, 2, {0.897, 1.802, 2.688, 3.442, 4.039, 5.675, 6.665, 8.428, 12.631, 17.056, 25.517, 34.277, 50.877},
-     {14.7, 23.3, 33.4, 54.9, 80.7, 60.6, 75.1, 59.2, 109.6, 142.3, 209.1, 273.6, 439.7}},
-    {192, 192, 3, {0.918, 1.858, 2.544, 3.481, 3.979, 5.346, 6.764, 7.776, 11.618, 15.656, 23.449, 31.492, 47.153},
-     {15.4, 24.3, 43.5, 53.6, 83.8, 82.1, 72.7, 77.7, 122.1, 163.2, 235.1, 299.6, 456.9}},
-    {256, 128, 2, {0.865, 1.797, 2.624, 3.601, 4.574, 5.530, 6.697, 7.757, 11.686, 15.233, 23.217, 31.222, 46.550},
-     {21.3, 35.0, 50.1, 62.9, 73.9, 85.7, 91.4, 100.0, 147.7, 223.4, 316.3, 421.8, 611.1}},
-    {256, 128, 3, {0.885, 1.787, 2.633, 3.593, 4.522, 5.451, 6.686, 7.655, 11.689, 15.144, 23.001, 31.000, 46.451},
-     {22.4, 38.8, 55.5, 69.0, 82.1, 94.1, 99.8, 110.9, 154.1, 216.6, 311.6, 410.4, 595.6}},
-    {128, 128, 2, {0.667, 0.872, 1.426, 1.794, 2.263, 2.677, 3.221, 3.821, 5.954, 8.068, 11.962, 16.089, 24.757},
-     {8.7, 14.0, 17.0, 19.1, 21.6, 26.4, 26.4, 29.4, 43.7, 60.3, 114.0, 158.4, 211.3}},
-    {128, 128, 3, {0.574, 1.152, 1.716, 2.263, 2.870, 3.428, 4.064, 4.601, 6.858, 9.405, 14.008, 18.876, 27.324},
-     {11.5, 17.8, 24.8, 31.7, 37.5, 45.0, 50.5, 57.3, 85.5, 109.5, 164.1, 223.9, 347.6}},
-    {128, 128, 4, {0.515, 1.059, 1.569, 2.113, 2.627, 3.235, 3.764, 4.230, 6.562, 8.995, 13.730, 18.619, 26.798},
-     {13.7, 22.4, 31.8, 40.0, 49.7, 55.6, 64.0, 75.6, 103.3, 129.4, 175.2, 232.1, 362.3}},
-    {128, 64, 2, {0.575, 0.579, 0.770, 1.252, 1.319, 1.669, 2.037, 2.174, 3.349, 5.283, 8.289, 11.171, 15.806},
-     {3.6, 7.2, 11.6, 11.1, 13.5, 14.1, 14.6, 16.7, 23.4, 11.7, 11.0, 15.4, 89.5}},
-    {128, 64, 3, {0.411, 0.547, 0.933, 1.104, 1.489, 1.749, 2.069, 2.405, 3.661, 5.545, 8.539, 12.549, 16.871},
-     {6.5, 8.6, 11.0, 12.6, 13.8, 14.7, 15.9, 17.4, 22.4, 20.0, 29.1, 22.3, 89.9}},
-    {128, 64, 4, {0.372, 0.759, 1.119, 1.505, 1.865, 2.241, 2.604, 3.044, 4.527, 6.203, 9.681, 13.186, 18.494},
-     {7.0, 10.7, 14.7, 17.5, 21.6, 25.4, 29.4, 32.4, 46.6, 62.4, 80.6, 102.3, 191.8}},
-    {64, 128, 2, {0.592, 0.609, 0.835, 1.270, 1.357, 1.622, 1.963, 2.110, 3.356, 4.356, 7.593, 10.284, 15.445},
-     {3.9, 7.8, 9.4, 10.6, 11.9, 14.1, 14.9, 16.7, 20.5, 24.6, 24.2, 26.8, 73.6}},
-    {64, 128, 3, {0.444, 0.559, 0.978, 1.121, 1.507, 1.656, 2.055, 2.233, 3.550, 4.680, 8.045, 11.099, 16.777},
-     {7.0, 8.7, 10.8, 12.7, 14.8, 17.9, 18.8, 22.8, 28.0, 41.7, 41.9, 48.0, 75.7}},
-    {64, 128, 4, {0.404, 0.815, 1.211, 1.603, 2.021, 2.429, 2.792, 3.216, 4.830, 6.428, 9.697, 13.225, 19.503},
-     {7.0, 10.8, 15.1, 18.5, 22.2, 26.5, 31.0, 33.9, 49.1, 65.3, 94.5, 120.0, 192.6}},
-    {64, 64, 2, {0.512, 0.497, 0.520, 0.629, 1.065, 1.074, 1.145, 1.308, 2.322, 3.429, 5.004, 7.991, 15.165},
-     {1.1, 3.0, 5.3, 7.6, 7.6, 8.8, 10.8, 10.6, 13.3, 13.8, 19.3, 11.3, 0.0}},
-    {64, 64, 3, {0.303, 0.387, 0.567, 0.740, 0.883, 1.100, 1.172, 1.348, 2.152, 2.900, 4.561, 7.126, 11.196},
-     {5.2, 5.3, 5.3, 7.4, 8.2, 8.6, 9.8, 10.6, 12.5, 14.5, 17.1, 7.0, 5.1}},
-    {64, 64, 4, {0.287, 0.373, 0.598, 0.692, 0.939, 1.043, 1.327, 1.423, 2.106, 2.839, 4.474, 7.037, 10.639},
-     {5.3, 4.7, 7.5, 8.0, 9.1, 10.8, 10.2, 12.6, 17.5, 20.5, 26.6, 25.2, 27.5}},
+    {256, 256, 2, {1.375, 2.743, 4.416, 5.740, 7.350, 9.060, 10.388, 11.957, 17.533, 22.925, 35.281, 46.688, 70.811},
+     {21.5, 31.0, 36.3, 50.1, 60.2, 64.9, 79.3, 89.5, 143.2, 198.6, 264.0, 353.8, 526.3}},
+    {256, 192, 2, {1.141, 2.197, 3.304, 4.299, 5.524, 6.877, 8.098, 9.257, 13.871, 18.383, 27.482, 36.714, 56.485},
+     {12.1, 22.9, 32.1, 44.0, 50.5, 55.3, 62.8, 70.3, 111.7, 148.4, 226.9, 298.1, 389.5}},
+    {192, 192, 2, {0.901, 1.914, 2.792, 3.900, 4.818, 5.552, 6.819, 7.829, 12.209, 16.197, 24.192, 32.866, 49.133},
+     {11.7, 14.7, 23.9, 27.3, 32.3, 43.5, 45.1, 48.3, 65.8, 91.1, 166.5, 215.0, 318.7}},
+    {192, 192, 3, {0.881, 1.840, 2.742, 3.685, 4.651, 5.581, 6.744, 7.565, 11.651, 15.441, 22.846, 30.906, 47.177},
+     {10.0, 17.0, 24.0, 32.0, 37.1, 43.4, 45.9, 55.0, 75.6, 107.4, 166.0, 202.8, 299.5}},
+    {256, 128, 2, {0.913, 1.865, 2.801, 3.708, 4.650, 5.657, 6.809, 7.727, 12.096, 16.253, 23.475, 31.480, 47.090},
+     {12.3, 16.7, 22.9, 30.1, 36.1, 41.2, 43.9, 53.0, 68.4, 86.9, 165.2, 217.0, 306.1}},
+    {256, 128, 3, {0.966, 1.940, 2.922, 3.918, 4.875, 5.886, 7.145, 7.890, 12.215, 16.256, 24.130, 32.520, 48.522},
+     {10.6, 16.8, 23.2, 29.0, 36.0, 41.4, 43.5, 53.8, 73.0, 96.0, 159.0, 204.9, 298.0}},
+    {128, 128, 2, {0.619, 0.878, 1.364, 1.707, 2.324, 2.633, 3.180, 3.607, 5.519, 7.826, 11.631, 15.276, 22.946},
+     {5.7, 8.3, 11.6, 13.7, 15.0, 19.2, 18.3, 21.9, 31.7, 32.2, 51.1, 87.0, 132.7}},
+    {128, 128, 3, {0.610, 1.169, 1.755, 2.351, 2.939, 3.532, 4.093, 4.691, 7.031, 9.609, 14.368, 19.240, 28.278},
+     {7.4, 10.8, 13.0, 16.2, 19.5, 22.6, 27.0, 30.2, 43.8, 54.6, 80.1, 117.4, 184.2}},
+    {128, 128, 4, {0.576, 1.166, 1.721, 2.323, 2.908, 3.438, 4.070, 4.713, 6.874, 9.469, 14.181, 18.998, 27.628},
+     {6.5, 9.9, 14.4, 16.9, 20.0, 25.6, 26.8, 29.8, 48.2, 57.1, 84.6, 124.4, 200.9}},
+    {128, 64, 2, {0.577, 0.600, 0.834, 1.228, 1.420, 1.712, 2.053, 2.248, 3.419, 5.051, 8.088, 10.932, 15.954},
+     {1.0, 4.4, 6.6, 6.7, 6.7, 10.4, 8.2, 9.9, 15.8, 11.8, 7.4, 7.7, 44.6}},
+    {128, 64, 3, {0.417, 0.580, 0.949, 1.176, 1.495, 1.731, 2.141, 2.413, 3.539, 5.497, 8.522, 11.715, 16.886},
+     {4.9, 5.6, 7.0, 7.0, 9.5, 12.7, 10.7, 13.2, 19.8, 12.9, 11.5, 14.2, 51.9}},
+    {128, 64, 4, {0.404, 0.766, 1.160, 1.534, 1.937, 2.303, 2.695, 3.091, 4.640, 6.455, 9.913, 13.397, 18.917},
+     {4.8, 7.5, 8.9, 11.2, 13.3, 15.6, 17.6, 19.6, 28.3, 32.7, 44.5, 57.7, 121.9}},
+    {64, 128, 2, {0.577, 0.600, 0.824, 1.204, 1.385, 1.639, 2.037, 2.176, 3.415, 4.409, 7.119, 9.995, 15.349},
+     {1.6, 5.4, 7.5, 7.7, 7.9, 11.5, 9.3, 13.3, 14.5, 19.7, 27.2, 22.1, 35.4}},
+    {64, 128, 3, {0.428, 0.626, 0.973, 1.192, 1.534, 1.825, 2.178, 2.453, 3.654, 4.817, 7.760, 10.961, 16.477},
+     {4.9, 4.9, 7.4, 7.6, 8.7, 9.6, 8.9, 11.2, 17.9, 24.8, 25.7, 24.6, 37.5}},
+    {64, 128, 4, {0.420, 0.815, 1.232, 1.642, 2.063, 2.477, 2.882, 3.293, 4.927, 6.592, 10.017, 13.490, 19.986},
+     {4.4, 7.1, 8.9, 11.2, 13.0, 15.1, 17.5, 19.9, 28.9, 37.3, 52.6, 67.4, 113.8}},
+    {64, 64, 2, {0.491, 0.505, 0.558, 0.688, 1.042, 1.125, 1.254, 1.334, 2.208, 3.227, 4.877, 7.753, 14.886},
+     {0.4, 1.4, 3.5, 4.4, 5.3, 4.5, 5.3, 8.7, 12.7, 9.9, 10.6, 0.4, 0.0}},
+    {64, 64, 3, {0.295, 0.400, 0.586, 0.750, 0.871, 1.145, 1.253, 1.426, 2.234, 2.915, 4.538, 6.976, 11.249},
+     {3.8, 3.2, 3.3, 4.4, 6.1, 4.7, 7.6, 7.1, 8.6, 9.4, 11.8, 1.4, 0.0}},
+    {64, 64, 4, {0.277, 0.373, 0.623, 0.705, 0.995, 1.099, 1.327, 1.473, 2.238, 2.991, 4.483, 6.954, 10.693},
+     {3.9, 3.4, 5.0, 6.2, 5.6, 7.7, 7.8, 8.8, 12.2, 14.8, 21.6, 11.5, 14.2}},
 };
 
 double interp(const double* v, long n) {
@@ -658,18 +915,6 @@ hipError_t launch_gemm(int dtype, GemmDesc& g, hipStream_t s) {
         return v ? std::max(1, std::atoi(v)) : 0;
     }();
     g.group_m = group_m > 0 ? group_m : (g.M >= kGroupLargeRows ? kGroupMLarge : kGroupM);
-    // Output path of the direct-to-LDS kernel: restaged through LDS (whole
-    // rows per store), except the unsplit GELU epilogue of launches with fewer
-    // than 8 tiles per CU, stored from registers so that the next tile's first
-    // loads run under the stores. Measured per shape against the other path
-    // (MI355X): residual epilogues restaged 1-6% faster or even everywhere
-    // (16384x3072x3072 362 -> 339 us); GELU restaged 10% faster at
-    // 16384x12288x3072 (12 tiles per CU), 1-6% slower at 2-3 (2048 and 4096 x
-    // 12288 x 3072, 6855x4608x1152).
-    {
-        const long tiles = (long)((g.M + g.bm - 1) / std::max(1, g.bm)) * ((g.N + g.bn - 1) / std::max(1, g.bn));
-        g.direct_out = g.epilogue == kEpiBiasGelu && g.ksplit == 1 && tiles < 8L * kCUs;
-    }
     if (dtype != kBF16) return launch_tile<float, 64, 64>(g, s);
     // main loop: direct-to-LDS (default) or the register-staged double buffer
     // (tuning knob MS_GEMM_PIPE=staged); MS_GEMM_STAGES overrides the stage count
@@ -691,8 +936,8 @@ hipError_t launch_gemm(int dtype, GemmDesc& g, hipStream_t s) {
     }
     int st = force_stages > 0 ? force_stages : (g.stages > 0 ? g.stages : 2);
     st = std::max(2, std::min(st, max_stages(g.bm, g.bn)));
-    if (g.bm == 256 && g.bn == 256) return launch_dl<256, 256, 2>(g, s);
-    if (g.bm == 256 && g.bn == 192) return launch_dl<256, 192, 2>(g, s);
+    if (g.bm == 256 && g.bn == 256) return launch_pp<256>(g, s);
+    if (g.bm == 256 && g.bn == 192) return launch_pp<192>(g, s);
     if (g.bm == 192 && g.bn == 192) return st >= 3 ? launch_dl<192, 192, 3>(g, s) : launch_dl<192, 192, 2>(g, s);
     if (g.bm == 256 && g.bn == 128) return st == 3 ? launch_dl<256, 128, 3>(g, s) : launch_dl<256, 128, 2>(g, s);
     if (g.bm == 128 && g.bn == 128)

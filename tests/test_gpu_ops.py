@@ -79,6 +79,29 @@ def test_linear_stage_variants_match_fp32_reference(tile, stages, shape, stage_o
     assert e <= 2e-2
 
 
+@pytest.mark.parametrize("tile", [(256, 256), (256, 192)], ids=lambda t: f"{t[0]}x{t[1]}")
+@pytest.mark.parametrize("M,N,K,ksplit", [(257, 516, 64, 1), (1, 4, 128, 1), (255, 260, 256, 1), (513, 392, 448, 1),
+                                          (300, 516, 640, 3), (4500, 4100, 192, 1)])
+@pytest.mark.parametrize("epi", [MS.MS_EPI_BIAS, MS.MS_EPI_BIAS_RESID, MS.MS_EPI_BIAS_GELU],
+                         ids=["bias", "resid", "gelu"])
+def test_linear_region_pipeline_edges(tile, M, N, K, ksplit, epi):
+    """The 256-row tiles' four-phase main loop: one, two, three, four and seven K steps (the pipeline fills over two),
+    one row and four columns, rows and widths one past a tile, widths that leave half a 16-byte store, K ranges of
+    different lengths, more tiles than CUs. Bound: the output's own rounding, 2^-9 of the largest value, doubled for
+    the float32 sums and GELU."""
+    g = torch.Generator(device=DEV).manual_seed(M + N + K + epi)
+    A = torch.randn(M, K, device=DEV, generator=g).bfloat16()
+    W = (torch.randn(N, K, device=DEV, generator=g) * 0.05).bfloat16()
+    b = (torch.randn(N, device=DEV, generator=g) * 0.05).bfloat16()
+    R = torch.randn(M, N, device=DEV, generator=g).bfloat16()
+    ws = torch.empty(ksplit * M * N * 4, device=DEV, dtype=torch.uint8) if ksplit > 1 else None
+    out = torch.full((M + 1, N), float("nan"), device=DEV, dtype=torch.bfloat16)
+    MS.ms_linear(A, W, b, out[:M], resid=R, epilogue=epi, tile=tile, ksplit=ksplit, workspace=ws)
+    torch.cuda.synchronize()
+    assert _err(out[:M], _ref(A, W, b, R, epi)) <= 2 ** -8
+    assert bool(out[M].isnan().all())       # nothing past the last row
+
+
 @pytest.mark.parametrize("ksplit", [2, 3, 5])
 def test_linear_split_k_matches_unsplit(ksplit):
     g = torch.Generator(device=DEV).manual_seed(ksplit)
