@@ -27,10 +27,18 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kKeyTile = 64;
 
-template <typename T, int HDP>
-__global__ __launch_bounds__(kThreads) void attention_kernel(AttnDesc a) {
+// float32 kernel, head_dim padded to HDP columns: 64 queries x one head x one key
+// range per workgroup. The float32 matrix instructions bound it (HDP / 16 x 32 of
+// them per 64-key tile and wave, 32 cycles each: 2.0 of 2.3 us per tile and
+// workgroup at head_dim 64) once four workgroups share a CU; before the key range
+// was split a small request ran on a few CUs, each tile in the 4.2 us of its own
+// loads, MFMAs and softmax one after the other.
+template <int HDP>
+__global__ __launch_bounds__(kThreads) void attention_f32_kernel(AttnDesc a) {
+    using T = float;
     using E = Elt<T>;
     using frag_t = typename E::frag_t;
+    static_assert(E::kKPerLane == 1, "one key slot per lane");
     constexpr int V = 16 / sizeof(T);            // elements per 16-byte vector
     constexpr int KLDS = HDP + V;                // padded K row (elements)
     constexpr int VLDS = kKeyTile + V;           // padded V^T row (elements)
@@ -45,6 +53,7 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(AttnDesc a) {
     const int grp = lane / 16;
     const int head = blockIdx.y;
     const int tile = blockIdx.x;
+    const int split = blockIdx.z;
     const int hd = a.hd, d = a.d, T_ = a.T;
 
     // segment of this query tile
@@ -74,16 +83,7 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(AttnDesc a) {
 #pragma unroll
     for (int kc = 0; kc < NKC; ++kc) {
         const int k = kc * E::kKStep + grp * E::kKPerLane;
-        if constexpr (E::kKPerLane == 1) {
-            qf[kc] = (qvalid && k < hd) ? q[(long)qrow * d + head * hd + k] : 0.f;
-        } else {
-            if (qvalid && k < hd) {
-                qf[kc] = *reinterpret_cast<const frag_t*>(q + (long)qrow * d + head * hd + k);
-            } else {
-                vec16 z = {{0u, 0u, 0u, 0u}};
-                qf[kc] = *reinterpret_cast<const frag_t*>(&z);
-            }
-        }
+        qf[kc] = (qvalid && k < hd) ? q[(long)qrow * d + head * hd + k] : 0.f;
     }
 
     f32x4_t oacc[NHS];
@@ -95,8 +95,9 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(AttnDesc a) {
     const long req_base = (long)b * T_;
     const int chunks = hd / V;                     // 16-byte chunks per key row
     const int ntiles = (T_ + kKeyTile - 1) / kKeyTile;
+    const int kt_end = min(ntiles, (split + 1) * a.tiles_per_split);
 
-    for (int kt = 0; kt < ntiles; ++kt) {
+    for (int kt = split * a.tiles_per_split; kt < kt_end; ++kt) {
         const int k0 = kt * kKeyTile;
         __syncthreads();
         for (int i = tid; i < kKeyTile * chunks; i += kThreads) {
@@ -142,12 +143,13 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(AttnDesc a) {
         mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
         const float m_new = fmaxf(m_run, mx);
         const float corr = (m_run == -INFINITY) ? 0.f : fast_exp2(m_run - m_new);
+        const float m_ref = m_new == -INFINITY ? 0.f : m_new;   // scores of -inf only so far: weights 0
         float psum = 0.f;
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                sc[ks][r] = fast_exp2(sc[ks][r] - m_new);
+                sc[ks][r] = fast_exp2(sc[ks][r] - m_ref);
                 psum += sc[ks][r];
             }
         l_run = l_run * corr + psum;
@@ -158,46 +160,27 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(AttnDesc a) {
             for (int r = 0; r < 4; ++r) oacc[h][r] *= corr;
 
         // O^T += V^T P^T
-        if constexpr (E::kKPerLane == 1) {
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
+        for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int key = ks * 16 + grp * 4 + r;
-#pragma unroll
-                    for (int h = 0; h < NHS; ++h) {
-                        const frag_t vf = sVt[(h * 16 + lane % 16) * VLDS + key];
-                        oacc[h] = E::mma(vf, sc[ks][r], oacc[h]);
-                    }
-                }
-        } else {
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                // slots 0..3: keys 32c + 4*grp + r; slots 4..7: keys 32c + 16 + 4*grp + r
-                union { bf16_t u[8]; frag_t f; } pf;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    pf.u[r] = f32_to_bf16(sc[2 * c][r]);
-                    pf.u[4 + r] = f32_to_bf16(sc[2 * c + 1][r]);
-                }
+            for (int r = 0; r < 4; ++r) {
+                const int key = ks * 16 + grp * 4 + r;
 #pragma unroll
                 for (int h = 0; h < NHS; ++h) {
-                    const T* row = &sVt[(h * 16 + lane % 16) * VLDS + 32 * c + 4 * grp];
-                    union { uint2 w[2]; frag_t f; } vf;
-                    vf.w[0] = *reinterpret_cast<const uint2*>(row);
-                    vf.w[1] = *reinterpret_cast<const uint2*>(row + 16);
-                    oacc[h] = E::mma(vf.f, pf.f, oacc[h]);
+                    const frag_t vf = sVt[(h * 16 + lane % 16) * VLDS + key];
+                    oacc[h] = E::mma(vf, sc[ks][r], oacc[h]);
                 }
             }
-        }
     }
 
     float l = l_run;
     l += __shfl_xor(l, 16, kWave);
     l += __shfl_xor(l, 32, kWave);
-    const float inv_l = 1.0f / l;
+    // a key range of weight 0 leaves zeros for the combine; the whole row's result stays 0 / 0
+    const float inv_l = a.nsplit > 1 && l == 0.f ? 0.f : 1.0f / l;
     if (qvalid) {
-        T* __restrict__ o = static_cast<T*>(a.o);
+        const long orow = (long)split * a.M + qrow;   // nsplit 1: the output row itself
+        T* __restrict__ o = a.nsplit > 1 ? a.part_o : static_cast<T*>(a.o);
 #pragma unroll
         for (int h = 0; h < NHS; ++h) {
             const int c = h * 16 + grp * 4;
@@ -205,9 +188,11 @@ __global__ __launch_bounds__(kThreads) void attention_kernel(AttnDesc a) {
                 float v[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) v[r] = oacc[h][r] * inv_l;
-                store4<T>(o + (long)qrow * d + head * hd + c, v);
+                store4<T>(o + orow * d + head * hd + c, v);
             }
         }
+        if (a.nsplit > 1 && grp == 0)
+            *reinterpret_cast<float2*>(a.part_ml + 2 * (orow * a.n_heads + head)) = make_float2(m_run, l);
     }
 }
 
@@ -632,8 +617,10 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
 // split count NS known at compile time every partial of the thread is loaded
 // before the first is used (NS = 0: any count, in chunks of 8). The arithmetic
 // and its order do not depend on NS.
-template <int NS>
+template <typename T, int NS>
 __global__ __launch_bounds__(256) void attention_combine_kernel(AttnDesc a) {
+    // running maxima: raw scores from the bf16 kernel, scaled to the log2 domain from the float32 one
+    const float mscale = sizeof(T) == 2 ? a.scale_log2 : 1.0f;
     const long n4 = (long)a.M * a.d / 4;
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n4) return;
@@ -646,7 +633,7 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(AttnDesc a) {
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     float L = 0.f;
     auto add = [&](float2 ml, float gmax, float4 po) {
-        const float w = fast_exp2((ml.x - gmax) * a.scale_log2) * ml.y;
+        const float w = fast_exp2((ml.x - gmax) * mscale) * ml.y;
         L += w;
         acc[0] += w * po.x; acc[1] += w * po.y; acc[2] += w * po.z; acc[3] += w * po.w;
     };
@@ -686,8 +673,11 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(AttnDesc a) {
     const float inv = 1.0f / L;
 #pragma unroll
     for (int r = 0; r < 4; ++r) acc[r] *= inv;
-    store4<bf16_t>(static_cast<bf16_t*>(a.o) + m * a.d + col, acc);
+    store4<T>(static_cast<T*>(a.o) + m * a.d + col, acc);
 }
+
+// Columns the float32 kernel pads a head to.
+int f32_head_cols(int hd) { return hd <= 32 ? 32 : hd <= 48 ? 48 : 64; }
 
 }  // namespace
 
@@ -701,7 +691,21 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(AttnDesc a) {
 // of 528 at 205 rows of 12 heads over 4096 keys (attention and combine 20.0 ->
 // 16.1 us), 512 instead of 640 at 1024 rows of 16 heads of 72 (38.7 -> 36.0)
 // and no split at 16 requests of 10 to 60% of 1024 keys (26.2 -> 22.7).
-double attention_cost_us(int base, int nsplit, int tps, int hd, int M, int d) {
+double attention_cost_us(int dtype, int base, int nsplit, int tps, int hd, int M, int d) {
+    // float32, measured the same way at head_dim 32, 40 and 64: a 64-key tile takes
+    // (0.030 + 0.036 k) us per padded column with k workgroups on a CU (the second
+    // term is the float32 matrix rate), a round 3.4 us + 0.8 per further workgroup.
+    // 205 rows of 4 heads of 64 over 1024 keys (16 workgroups unsplit) 67 -> 9 us
+    // with the combine, 410 rows of 4 heads over 4096 keys 290 -> 36 us.
+    if (dtype != kBF16) {
+        const int hdp = f32_head_cols(hd), per_cu = hdp == 32 ? 8 : hdp == 48 ? 6 : 4;
+        const long groups = (long)base * nsplit, slots = 256L * per_cu, rest = groups % slots;
+        auto round_us = [&](long k) { return 3.4 + 0.8 * (k - 1) + tps * hdp * (0.030 + 0.036 * k); };
+        double us = (double)(groups / slots) * round_us(per_cu);
+        if (rest) us += round_us((rest + 255) / 256);
+        if (nsplit > 1) us += 2.5 + 0.1 * nsplit + (4.0 * nsplit + 4) * M * d / 6.0e6;
+        return us;
+    }
     const int per_cu = hd <= 16 ? 5 : hd <= 48 ? 4 : hd <= 88 ? 3 : 2;
     const int mfmas = 8 * ((hd + 31) / 32) + 4 * ((hd + 15) / 16 + (hd % 16 == 0));
     const double unit = mfmas * (hd % 16 ? 1.12 : 1.0);
@@ -715,7 +719,7 @@ double attention_cost_us(int base, int nsplit, int tps, int hd, int M, int d) {
 
 // bf16, head_dim a multiple of 8 up to 128: the direct-to-LDS kernel (its
 // partials combined below when the key range is split). fp32, head_dim up to
-// 64: the register-staged kernel.
+// 64: the register-staged kernel, its key range split and combined the same way.
 hipError_t launch_attention(int dtype, const AttnDesc& a, hipStream_t s) {
     if (a.M == 0) return hipSuccess;
     dim3 block(kThreads);
@@ -730,25 +734,31 @@ hipError_t launch_attention(int dtype, const AttnDesc& a, hipStream_t s) {
         }
     } else {
         if (a.hd > 64) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((attention_kernel<float, 64>), dim3(a.n_qtiles, a.n_heads), block, 0, s, a);
+        const dim3 grid(a.n_qtiles, a.n_heads, a.nsplit);
+        const int cols = f32_head_cols(a.hd);
+        if (cols == 32) hipLaunchKernelGGL((attention_f32_kernel<32>), grid, block, 0, s, a);
+        else if (cols == 48) hipLaunchKernelGGL((attention_f32_kernel<48>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((attention_f32_kernel<64>), grid, block, 0, s, a);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_attention_combine(int dtype, const AttnDesc& a, hipStream_t s) {
-    if (a.M == 0 || a.nsplit <= 1) return hipSuccess;
+template <typename T>
+void launch_combine(const AttnDesc& a, hipStream_t s) {
     const long n4 = (long)a.M * a.d / 4;
     const dim3 grid((unsigned)((n4 + 255) / 256)), block(256);
     switch (a.nsplit) {
-        case 2: hipLaunchKernelGGL(attention_combine_kernel<2>, grid, block, 0, s, a); break;
-        case 3: hipLaunchKernelGGL(attention_combine_kernel<3>, grid, block, 0, s, a); break;
-        case 4: hipLaunchKernelGGL(attention_combine_kernel<4>, grid, block, 0, s, a); break;
-        case 5: hipLaunchKernelGGL(attention_combine_kernel<5>, grid, block, 0, s, a); break;
-        case 6: hipLaunchKernelGGL(attention_combine_kernel<6>, grid, block, 0, s, a); break;
-        case 7: hipLaunchKernelGGL(attention_combine_kernel<7>, grid, block, 0, s, a); break;
-        case 8: hipLaunchKernelGGL(attention_combine_kernel<8>, grid, block, 0, s, a); break;
-        default: hipLaunchKernelGGL(attention_combine_kernel<0>, grid, block, 0, s, a); break;
+#define MS_NS(n) case n: hipLaunchKernelGGL((attention_combine_kernel<T, n>), grid, block, 0, s, a); break;
+        MS_NS(2) MS_NS(3) MS_NS(4) MS_NS(5) MS_NS(6) MS_NS(7) MS_NS(8)
+#undef MS_NS
+        default: hipLaunchKernelGGL((attention_combine_kernel<T, 0>), grid, block, 0, s, a); break;
     }
+}
+
+hipError_t launch_attention_combine(int dtype, const AttnDesc& a, hipStream_t s) {
+    if (a.M == 0 || a.nsplit <= 1) return hipSuccess;
+    if (dtype == kBF16) launch_combine<bf16_t>(a, s);
+    else launch_combine<float>(a, s);
     return hipGetLastError();
 }
 

@@ -18,7 +18,7 @@
 // bf16 tiles: BM x BN from 64 x 64 to 256 x 256, operands copied global ->
 // LDS without staging registers into 2-4 stages of 64-deep K steps, the 256 x
 // 256 and 256 x 192 ones refilled region by region (gemm_pp_kernel); fp32:
-// 64 x 64 tiles through registers, double-buffered. The host picks tile,
+// 64 x 64 or 32 x 32 tiles through registers, double-buffered. The host picks tile,
 // stage count and K split from a step-time table measured on MI355X; split
 // workgroups write float32 partials, summed in a fixed order by a second
 // kernel that applies the epilogue (or, before a LayerNorm, by the fused
@@ -859,11 +859,44 @@ double interp(const double* v, long n) {
             return v[i - 1] + (v[i] - v[i - 1]) * (double)(n - kCostAt[i - 1]) / (kCostAt[i] - kCostAt[i - 1]);
     return v[kCostN - 1] * (double)n / kCostAt[kCostN - 1];
 }
+// The same for float32, per 32-deep step (bias epilogue, K = 256 and 1024). 32 x 32
+// tiles are the quicker ones while the launch is short of workgroups (a step waits
+// for its loads: 0.36 us against 0.76 at n = 1), 64 x 64 read half as much per
+// product. Before, 64 x 64 and no K split: 205x256x1024 26 -> 8 us, 205x768x256
+// 9.3 -> 5.1, 800x512x2048 50 -> 30, 3000x512x2048 82 -> 67.
+constexpr TileCost kCostF32[] = {
+    {64, 64, 2, {0.76, 1.34, 1.85, 2.43, 2.95, 3.45, 4.05, 4.62, 6.63, 8.90, 13.0, 17.1, 25.6},
+     {4.0, 5.1, 6.8, 7.0, 10.0, 12.0, 10.5, 9.5, 13.8, 14.6, 23.0, 32.0, 48.0}},
+    {32, 32, 2, {0.356, 0.483, 0.693, 0.882, 1.07, 1.26, 1.44, 1.63, 2.31, 3.15, 4.50, 5.74, 8.60},
+     {2.35, 2.45, 2.78, 2.92, 3.2, 3.5, 3.9, 4.3, 6.3, 6.5, 8.0, 10.2, 15.0}},
+};
+
+GemmPlan plan_f32(int M, int N, int K, size_t part_capacity_floats) {
+    GemmPlan p{64, 64, 1, 2};
+    const int steps = K / 32;
+    double best = 1e30;
+    for (const TileCost& c : kCostF32) {
+        const long grp = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+        for (int ks = 1; ks <= 8 && ks <= steps; ++ks) {
+            if (ks > 1 && (size_t)ks * M * N > part_capacity_floats) break;
+            const int per = (steps + ks - 1) / ks;
+            const long n = (grp * ks + kCUs - 1) / kCUs;
+            double us = per * interp(c.step, n) + interp(c.tile, n);
+            // partial sums: 2.1 us at two planes of 205 x 256, 4.0 at eight
+            if (ks > 1) us += 2.0 + 0.25 * ks + ((double)ks * 4 + 4) * M * N / 4.0e6;
+            if (us < best * 0.97) {
+                best = us;
+                p = GemmPlan{c.bm, c.bn, ks, c.stages};
+            }
+        }
+    }
+    return p;
+}
 }  // namespace
 
 GemmPlan plan_gemm(int dtype, int M, int N, int K, size_t part_capacity_floats) {
     GemmPlan p{64, 64, 1, 2};
-    if (dtype != kBF16) return p;   // fp32 path: one tile shape
+    if (dtype != kBF16) return plan_f32(M, N, K, part_capacity_floats);
     const int steps = K / 64;
     double best = 1e30;
     static const double split_scale = [] {   // tuning knob MS_GEMM_SPLIT_COST: scales the split-K pass cost
@@ -915,7 +948,7 @@ hipError_t launch_gemm(int dtype, GemmDesc& g, hipStream_t s) {
         return v ? std::max(1, std::atoi(v)) : 0;
     }();
     g.group_m = group_m > 0 ? group_m : (g.M >= kGroupLargeRows ? kGroupMLarge : kGroupM);
-    if (dtype != kBF16) return launch_tile<float, 64, 64>(g, s);
+    if (dtype != kBF16) return g.bm == 32 ? launch_tile<float, 32, 32>(g, s) : launch_tile<float, 64, 64>(g, s);
     // main loop: direct-to-LDS (default) or the register-staged double buffer
     // (tuning knob MS_GEMM_PIPE=staged); MS_GEMM_STAGES overrides the stage count
     static const bool staged = [] {

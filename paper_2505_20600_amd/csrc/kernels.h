@@ -98,7 +98,7 @@ struct AttnDesc {
     const int32_t* cu_tiles;
     int nseg, T, d, hd, n_qtiles, n_heads;
     float scale_log2;     // log2(e) / sqrt(hd)
-    // bf16 path: 128-row query tiles, keys split over `nsplit` workgroups of
+    // query tiles of 128 rows (bf16) or 64 (float32), keys split over `nsplit` workgroups of
     // `tiles_per_split` 64-key tiles; partials (O normalised by its own key
     // range's sum, and that range's running max and sum, all float32) go to
     // part_o [nsplit][M][d] / part_ml [nsplit][M][n_heads].
@@ -111,9 +111,9 @@ struct AttnDesc {
 // (when the key range is split, the partials are left for launch_attention_combine).
 hipError_t launch_attention(int dtype, const AttnDesc& a, hipStream_t s);
 
-// Modelled time of the bf16 attention and its combine for `base` query tiles x
+// Modelled time of the attention and its combine for `base` query tiles x
 // heads, their keys in `nsplit` ranges of `tps` 64-key tiles.
-double attention_cost_us(int base, int nsplit, int tps, int hd, int M, int d);
+double attention_cost_us(int dtype, int base, int nsplit, int tps, int hd, int M, int d);
 
 // Combine of the key-range partials (no-op when nsplit == 1).
 hipError_t launch_attention_combine(int dtype, const AttnDesc& a, hipStream_t s);

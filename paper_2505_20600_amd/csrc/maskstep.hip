@@ -352,16 +352,17 @@ void finish_packing(Packing& p, const ms_model_desc& desc, int batch, int T, int
         p.n_qtiles_fast += (len + ms::kFastQTile - 1) / ms::kFastQTile;
     }
     const int ntiles = (T + 63) / 64;
-    const int base = std::max(1, p.n_qtiles_fast * desc.n_heads);
+    const bool bf16 = desc.dtype == MS_BF16;
+    const int base = std::max(1, (bf16 ? p.n_qtiles_fast : p.n_qtiles) * desc.n_heads);
     const size_t part_rows = std::min(attn_part_rows(desc, batch), attn_part_o_rows(desc, batch));
-    const int most = p.M > 0 && desc.dtype == MS_BF16 ? std::max(1, std::min(ntiles, (int)(part_rows / p.M))) : 1;
+    const int most = p.M > 0 ? std::max(1, std::min(ntiles, (int)(part_rows / p.M))) : 1;
     int ns = 1;
     if (const char* ev = std::getenv("MS_ATTN_SPLIT_TARGET")) {   // tuning knob: workgroups to reach
         ns = std::min(most, std::max(1, (std::max(1, std::atoi(ev)) + base - 1) / base));
     } else {
         double best = 1e30;
         for (int k = 1; k <= most; ++k) {
-            const double us = ms::attention_cost_us(base, k, (ntiles + k - 1) / k, hd, p.M, desc.d_model);
+            const double us = ms::attention_cost_us(desc.dtype, base, k, (ntiles + k - 1) / k, hd, p.M, desc.d_model);
             if (us < best) {
                 best = us;
                 ns = k;

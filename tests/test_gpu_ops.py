@@ -149,6 +149,37 @@ def test_linear_fp32_matches_reference():
     assert e <= 1e-4
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 4, 32), (31, 36, 64), (33, 68, 1024), (205, 256, 1024), (65, 1028, 2080),
+                                   (1030, 2052, 96), (3000, 516, 2048)])
+@pytest.mark.parametrize("split", [False, True], ids=["unsplit", "may-split"])
+@pytest.mark.parametrize("epi", [MS.MS_EPI_BIAS, MS.MS_EPI_BIAS_RESID, MS.MS_EPI_BIAS_GELU],
+                         ids=["bias", "resid", "gelu"])
+def test_linear_fp32_planned_tiles(M, N, K, split, epi):
+    """The float32 tiles and K splits the planner picks: rows and columns one past a 32- or 64-wide tile, one K step,
+    K ranges of different lengths, a workspace that allows a split and none. Bound, element by element: a float32 sum
+    of K + 2 terms, each step of it rounded once (|A| |W|^T + |b| + |R| times (K + 2) 2^-24), GELU's slope of at most
+    1.13 and its own 3.3e-7 of the value's magnitude."""
+    g = torch.Generator(device=DEV).manual_seed(M + N + K + epi)
+    A = torch.randn(M, K, device=DEV, generator=g)
+    W = torch.randn(N, K, device=DEV, generator=g) * 0.05
+    b = torch.randn(N, device=DEV, generator=g)
+    R = torch.randn(M, N, device=DEV, generator=g)
+    ws = torch.empty(8 * M * N * 4, device=DEV, dtype=torch.uint8) if split else None
+    out = torch.full((M + 1, N), float("nan"), device=DEV)
+    MS.ms_linear(A, W, b, out[:M], resid=R, epilogue=epi, workspace=ws)
+    torch.cuda.synchronize()
+    ref = A.double() @ W.double().t().contiguous() + b.double()
+    mag = A.double().abs() @ W.double().abs().t().contiguous() + b.double().abs()
+    bound = (K + 2) * 2.0 ** -24 * (mag + (R.double().abs() if epi == MS.MS_EPI_BIAS_RESID else 0.0))
+    if epi == MS.MS_EPI_BIAS_RESID:
+        ref = ref + R.double()
+    if epi == MS.MS_EPI_BIAS_GELU:
+        bound = 1.13 * bound + 3.3e-7 * (1.0 + ref.abs())
+        ref = F.gelu(ref)
+    assert bool(((out[:M].double() - ref).abs() <= bound).all())
+    assert bool(out[M].isnan().all())       # nothing past the last row
+
+
 def test_linear_rejects_bad_arguments():
     A = torch.zeros(8, 64, device=DEV, dtype=torch.bfloat16)
     W = torch.zeros(8, 64, device=DEV, dtype=torch.bfloat16)
