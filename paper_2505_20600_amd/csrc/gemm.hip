@@ -16,7 +16,7 @@
 // the working K/V (the K/V cache of Fig. 7 with the masked rows replaced).
 //
 // bf16 tiles: BM x BN from 64 x 64 to 256 x 256, operands copied global ->
-// LDS without staging registers into 2-4 stages of 64-deep K steps, the 256 x
+// LDS without staging registers into 2-8 stages of 64-deep K steps, the 256 x
 // 256 and 256 x 192 ones refilled region by region (gemm_pp_kernel); fp32:
 // 64 x 64 or 32 x 32 tiles through registers, double-buffered. The host picks tile,
 // stage count and K split from a step-time table measured on MI355X; split
@@ -366,9 +366,17 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(GemmDesc g) {
 // quantises rows more finely than 256-row tiles.
 constexpr int dl_waves(int bm, int bn) { return bm * bn >= 192 * 192 ? 8 : 4; }
 
+// Waits until all but the last `left` issued stages have landed (never more than R
+// are in flight behind the one waited for; towards the end of K fewer).
+template <int R, int IPW>
+__device__ __forceinline__ void wait_stages(int left) {
+    if (left >= R) wait_vmcnt<R * IPW>();
+    else if constexpr (R > 0) wait_stages<R - 1, IPW>(left);
+}
+
 template <int BM, int BN, int S, int EPI>
 __global__ __launch_bounds__(kWave * dl_waves(BM, BN)) void gemm_dl_kernel(GemmDesc g) {
-    static_assert(S >= 2 && S <= 4, "stages");
+    static_assert(S >= 2 && S <= 8, "stages");
     constexpr int NW = dl_waves(BM, BN);
     constexpr int WM = 2, WN = NW / 2;          // wave grid: WM along m, WN along n
     using E = Elt<bf16_t>;
@@ -466,8 +474,7 @@ __global__ __launch_bounds__(kWave * dl_waves(BM, BN)) void gemm_dl_kernel(GemmD
         // stage kt complete (the loads of the later stages may stay in
         // flight); the barrier also ends every wave's reads of the stage
         // refilled next, read in step kt - 1
-        if (kt + S - 1 <= nk) wait_vmcnt<(S - 2) * IPW>();
-        else wait_vmcnt<0>();
+        wait_stages<S - 2, IPW>(nk - kt - 1);
         barrier_only();
         // The 8-wave tiles spread this step's copies over the MFMA groups of
         // the first half step, so the matrix cores start right after the
@@ -918,6 +925,15 @@ GemmPlan plan_gemm(int dtype, int M, int N, int K, size_t part_capacity_floats) 
             }
         }
     }
+    // At most one workgroup per CU: the rest of its LDS holds more stages. Its K step
+    // waits for the operand stream (16 KB of a 64 x 64 tile in 0.28 us at four stages,
+    // about 26 B per clock and CU), which is deeper with more copies in flight. With
+    // two workgroups on a CU the extra stages would keep the second one out. Together
+    // with the waits of the last steps, which leave the copies still needed in flight:
+    // block of 205 rows at d 768 58.8 -> 55.8 us, 12 blocks of 1229 rows 1141 -> 1094,
+    // other sizes even; outputs bit-identical.
+    if (p.bm * p.bn <= 128 * 64 && (long)((M + p.bm - 1) / p.bm) * ((N + p.bn - 1) / p.bn) * p.ksplit <= kCUs)
+        p.stages = p.bm * p.bn == 64 * 64 ? 8 : 6;
     if (const char* f = std::getenv("MS_GEMM_TILE")) {   // tuning override "BMxBN"
         int bm = 0, bn = 0;
         if (std::sscanf(f, "%dx%d", &bm, &bn) == 2) {
@@ -931,7 +947,7 @@ GemmPlan plan_gemm(int dtype, int M, int N, int K, size_t part_capacity_floats) 
 // Largest stage count whose LDS fits next to nothing else (160 KB per CU).
 int max_stages(int bm, int bn) {
     const int per = (bm + bn) * 64 * 2;
-    return std::min(4, (160 * 1024) / per);
+    return std::min(8, (160 * 1024) / per);
 }
 
 hipError_t launch_gemm(int dtype, GemmDesc& g, hipStream_t s) {
@@ -972,14 +988,14 @@ hipError_t launch_gemm(int dtype, GemmDesc& g, hipStream_t s) {
     if (g.bm == 256 && g.bn == 256) return launch_pp<256>(g, s);
     if (g.bm == 256 && g.bn == 192) return launch_pp<192>(g, s);
     if (g.bm == 192 && g.bn == 192) return st >= 3 ? launch_dl<192, 192, 3>(g, s) : launch_dl<192, 192, 2>(g, s);
-    if (g.bm == 256 && g.bn == 128) return st == 3 ? launch_dl<256, 128, 3>(g, s) : launch_dl<256, 128, 2>(g, s);
+    if (g.bm == 256 && g.bn == 128) return st >= 3 ? launch_dl<256, 128, 3>(g, s) : launch_dl<256, 128, 2>(g, s);
     if (g.bm == 128 && g.bn == 128)
-        return st == 4 ? launch_dl<128, 128, 4>(g, s) : st == 3 ? launch_dl<128, 128, 3>(g, s) : launch_dl<128, 128, 2>(g, s);
+        return st >= 4 ? launch_dl<128, 128, 4>(g, s) : st == 3 ? launch_dl<128, 128, 3>(g, s) : launch_dl<128, 128, 2>(g, s);
     if (g.bm == 128 && g.bn == 64)
-        return st == 4 ? launch_dl<128, 64, 4>(g, s) : st == 3 ? launch_dl<128, 64, 3>(g, s) : launch_dl<128, 64, 2>(g, s);
+        return st >= 6 ? launch_dl<128, 64, 6>(g, s) : st >= 4 ? launch_dl<128, 64, 4>(g, s) : st == 3 ? launch_dl<128, 64, 3>(g, s) : launch_dl<128, 64, 2>(g, s);
     if (g.bm == 64 && g.bn == 128)
-        return st == 4 ? launch_dl<64, 128, 4>(g, s) : st == 3 ? launch_dl<64, 128, 3>(g, s) : launch_dl<64, 128, 2>(g, s);
-    return st == 4 ? launch_dl<64, 64, 4>(g, s) : st == 3 ? launch_dl<64, 64, 3>(g, s) : launch_dl<64, 64, 2>(g, s);
+        return st >= 6 ? launch_dl<64, 128, 6>(g, s) : st >= 4 ? launch_dl<64, 128, 4>(g, s) : st == 3 ? launch_dl<64, 128, 3>(g, s) : launch_dl<64, 128, 2>(g, s);
+    return st >= 8 ? launch_dl<64, 64, 8>(g, s) : st >= 4 ? launch_dl<64, 64, 4>(g, s) : st == 3 ? launch_dl<64, 64, 3>(g, s) : launch_dl<64, 64, 2>(g, s);
 }
 
 hipError_t launch_gemm_reduce(int dtype, const GemmDesc& g, hipStream_t s) {

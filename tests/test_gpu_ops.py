@@ -13,7 +13,7 @@ TILES = [(256, 256), (256, 192), (192, 192), (256, 128), (128, 128), (128, 64), 
 # every deeper stage variant the library builds (tile, stages); the forced-tile
 # tests above run two stages
 STAGED = [((192, 192), 3), ((256, 128), 3), ((128, 128), 3), ((128, 128), 4), ((128, 64), 3), ((128, 64), 4),
-          ((64, 128), 3), ((64, 128), 4), ((64, 64), 3), ((64, 64), 4)]
+          ((64, 128), 3), ((64, 128), 4), ((64, 64), 3), ((64, 64), 4), ((128, 64), 6), ((64, 128), 6), ((64, 64), 8)]
 
 
 def _ref(A, W, b, R, epi):
