@@ -1,5 +1,7 @@
 """Kernel-level parity of the row GEMM (every tile shape, split-K, each epilogue)
 against a float32 PyTorch reference of the same operation."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -100,6 +102,31 @@ def test_linear_region_pipeline_edges(tile, M, N, K, ksplit, epi):
     torch.cuda.synchronize()
     assert _err(out[:M], _ref(A, W, b, R, epi)) <= 2 ** -8
     assert bool(out[M].isnan().all())       # nothing past the last row
+
+
+@pytest.mark.parametrize("dtype,tile,ksplit", [("bf16", (256, 256), 1), ("bf16", (192, 192), 1), ("bf16", (64, 64), 1),
+                                               ("bf16", (128, 64), 2), ("fp32", (0, 0), 1), ("fp32", (0, 0), 2)])
+def test_gelu_of_huge_and_infinite_values(dtype, tile, ksplit):
+    """Pre-activations that are or overflow to +inf, and finite ones up to the type's largest: GELU is x above 30 and 0
+    below -30 (Phi(-30) < 1e-197) to the output's rounding, +inf at +inf, and NaN at -inf and NaN as x (1 + erf) is."""
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    big = torch.finfo(dt).max
+    cols = torch.tensor([math.inf, -math.inf, big, -big, 1e30, -1e30, 1e19, -1e19, 1e5, -1e5, 30.0, -30.0, math.nan, 0.0,
+                         big, -big], device=DEV).to(dt)
+    M, N, K = 65, 64, 128
+    b = cols.repeat(N // cols.numel())
+    A = torch.zeros(M, K, device=DEV, dtype=dt)
+    W = torch.zeros(N, K, device=DEV, dtype=dt)
+    A[1, 0], W[:, 0] = big, 4.0             # row 1: the products overflow to +inf
+    ws = torch.empty(ksplit * M * N * 4, device=DEV, dtype=torch.uint8) if ksplit > 1 else None
+    out = torch.empty(M, N, device=DEV, dtype=dt)
+    MS.ms_linear(A, W, b, out, epilogue=MS.MS_EPI_BIAS_GELU, tile=tile, ksplit=ksplit, workspace=ws)
+    torch.cuda.synchronize()
+    pre = (A.double() @ W.double().t().contiguous()).float() + b.float()
+    want = torch.where(pre > 0, pre, pre * 0.0).to(dt).float()     # -inf * 0 and NaN * 0 are NaN
+    assert bool(((out.float() - want).nan_to_num(0.0).abs() <= 2 ** -8 * want.abs().nan_to_num(0.0, 0.0)).all())
+    assert torch.equal(out.isnan(), want.isnan())
+    assert torch.equal(out.isinf(), want.isinf())
 
 
 @pytest.mark.parametrize("ksplit", [2, 3, 5])
