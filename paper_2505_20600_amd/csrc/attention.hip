@@ -233,8 +233,9 @@ __device__ __forceinline__ f32x4_t mfma32(bf16x8_t a, bf16x8_t b, f32x4_t c) {
 // exponentials at 8.6 cycles and ~110 other VALU instructions at 3-5, against
 // 576 MFMA cycles at head_dim 64 and 1088 at 128), of which only a part runs
 // under another wave's MFMAs, and the start and end of each workgroup. The
-// running maximum is subtracted by starting the score accumulators at -m, and
-// its row reduction runs only when some lane's maximum calls for a rescale.
+// running maximum is subtracted by starting the score accumulators at -m (in the
+// exponent's FMA instead of there: 329 -> 333 us for a block of 4096 rows at d 1152),
+// and its row reduction runs only when some lane's maximum calls for a rescale.
 // Measured at 4 x ~1450 rows of 24 heads of 128 over 4608 keys 364 -> 339 us,
 // 4096 rows of 16 heads of 72 over 4096 keys 103 (with combine) -> 95 us; the
 // head_dims that had a register-staged kernel before: 96 with 2.6k rows of 12
@@ -244,6 +245,11 @@ __device__ __forceinline__ f32x4_t mfma32(bf16x8_t a, bf16x8_t b, f32x4_t c) {
 // ---------------------------------------------------------------------------
 
 constexpr float kRescaleLog2 = 8.0f;   // softmax weights may reach 2^8 before a rescale
+// Score accumulators start at minus the running maximum, but not beyond this: a score
+// far above the maximum so far would be rounded to the digits of the latter (a first
+// key tile near the type's lowest value left the others' scores none). 2^14 leaves them
+// 2^-10, below the rounding of the weights, and a tile's ordinary path as it was.
+constexpr float kStartMax = 16384.0f;
 
 template <int HD>
 struct DmaCfg {
@@ -400,13 +406,14 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
 #pragma unroll
         for (int h = 0; h < C::NHS; ++h) oacc[qb][h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const float cs = a.scale_log2, rescale_at = kRescaleLog2 / cs;
-    // running maximum per query, subtracted from the scores by starting their
-    // accumulators at -m
-    float m_run[2] = {0.f, 0.f};
+    // running maximum per query (-inf: no score above -inf yet); the scores' accumulators
+    // start at negm, minus the maximum within +-kStartMax
+    float m_run[2] = {-INFINITY, -INFINITY};
     f32x4_t negm[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+    bool beyond = true;   // some query's maximum lies beyond it: every tile is shifted
     const bf16x8_t onesf = __builtin_bit_cast(bf16x8_t, make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
 
-    // S^T - m of one tile (QK^T) into sacc, keys past T masked
+    // S^T + negm of one tile (QK^T) into sacc, keys past T masked
     auto qk = [&](uint32_t sbase, int k0, bool tail, f32x4_t (&sacc)[2][4]) {
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)
@@ -434,7 +441,7 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
         }
     };
     // online softmax in place: sacc becomes the weights; running maxima and accumulators updated
-    auto softmax = [&](f32x4_t (&sacc)[2][4], bool first) {
+    auto softmax = [&](f32x4_t (&sacc)[2][4]) {
         // Rescale only when some score exceeds its query's running maximum by
         // more than 8 in the exp2 domain: below that the stale maximum
         // keeps the weights <= 256, exact in bf16 and fp32 alike, and numerator
@@ -449,23 +456,30 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
                 mx[qb] = fmaxf(fmaxf(mx[qb], sacc[qb][i / 4][i % 4]), sacc[qb][(i + 1) / 4][(i + 1) % 4]);
             mx[qb] = fmaxf(mx[qb], sacc[qb][3][3]);
         }
-        if (first || __any(fmaxf(mx[0], mx[1]) > rescale_at)) {
+        if (beyond || __any(fmaxf(mx[0], mx[1]) > rescale_at)) {
+            bool far = false;
 #pragma unroll
             for (int qb = 0; qb < 2; ++qb) {
                 const float rm = rows_max(mx[qb]);
-                const float up = first ? rm : fmaxf(rm, 0.f);
-                if (!first) {
-                    const float corr = fast_exp2(-up * cs);
+                const bool none = m_run[qb] == -INFINITY;
+                // the scores' new maximum and the old one, both less the accumulators' start
+                const float was = none ? -INFINITY : m_run[qb] + negm[qb][0];
+                const float up = fmaxf(rm, was);
+                const bool still = up == -INFINITY;   // weights exp2(-inf) = 0
+                const float corr = none ? 0.f : fast_exp2((was - up) * cs);
 #pragma unroll
-                    for (int h = 0; h < C::NHS; ++h) oacc[qb][h] *= corr;
-                }
-                m_run[qb] += up;
-                negm[qb] = f32x4_t{-m_run[qb], -m_run[qb], -m_run[qb], -m_run[qb]};
+                for (int h = 0; h < C::NHS; ++h) oacc[qb][h] *= corr;
+                m_run[qb] = fmaxf(m_run[qb], rm - negm[qb][0]);
+                const float n = m_run[qb] == -INFINITY ? 0.f : -fminf(fmaxf(m_run[qb], -kStartMax), kStartMax);
+                negm[qb] = f32x4_t{n, n, n, n};
+                far |= fabsf(m_run[qb]) > kStartMax;
+                const float off = still ? 0.f : up;
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) sacc[qb][ks][r] -= up;
+                    for (int r = 0; r < 4; ++r) sacc[qb][ks][r] -= off;
             }
+            beyond = __any(far);
         }
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)
@@ -541,7 +555,7 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
         const int kt = kt0 + t;
         if (!active) continue;   // every row of this wave lies past the segment: it only copies
         qk((t % S) * C::STAGEB, kt * kKeyTile, kt >= kfull, sa);
-        softmax(sa, t == 0);
+        softmax(sa);
         pv((t % S) * C::STAGEB, sa);
     }
 
@@ -569,8 +583,8 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
             l = oacc[qb][C::NHS - 1][0];
         }
         // normalised by this key range's own sum; bf16 rows of the output, or
-        // float32 rows of the partial
-        const float inv_l = 1.0f / l;
+        // float32 rows of the partial (zeros for a range of weight 0)
+        const float inv_l = a.nsplit > 1 && l == 0.f ? 0.f : 1.0f / l;
         const int rl = qb * 16 + l16;
 #pragma unroll
         for (int h = 0; h < C::NHS; ++h) {

@@ -38,3 +38,41 @@ def test_block_at_every_head_dim_matches_oracle(hd, dtype, split, monkeypatch):
     y_ref, kv_ref = oracle.masked_stack(x, mask, kv, yc, ws, shape, return_kv=True, round_p=dtype == "bf16")
     G.assert_close(y, y_ref, dtype, f"head_dim {hd} output", blocks=1, inp=x)
     G.assert_close(kv_gpu[0], kv_ref[0], dtype, f"head_dim {hd} K/V", blocks=1)
+
+
+@pytest.mark.parametrize("hd,dtype", [(40, "bf16"), (64, "bf16"), (72, "bf16"), (128, "bf16"), (64, "fp32")])
+@pytest.mark.parametrize("split", ["1", "100000"], ids=["unsplit", "split"])
+@pytest.mark.parametrize("far", [(0,), (1,), (0, 1)], ids=["first", "second", "first-two"])
+def test_key_tiles_far_from_the_others_match_oracle(hd, dtype, split, far, monkeypatch):
+    """Three key tiles; every cached key of the tiles `far` scores -inf, the type's lowest value, large negative or
+    large positive values against every query (one request each, the last with plain keys), so that a whole key range
+    weighs nothing, or all others do, and a maximum jumps by far more than a score's digits hold. The queries are
+    a bias in one column, so that the scores are products of two numbers."""
+    monkeypatch.setenv("MS_ATTN_SPLIT_TARGET", split)
+    lowest = -3.3895313892515355e38      # bf16; float32's own is below it
+    values = [-np.inf, lowest, -2e37, -1e7, 1e12, None]
+    d = hd * 64 // math.gcd(hd, 64)
+    shape = W.ModelShape(f"far{hd}", 1, d, d // hd, 2, 9, 15, dtype=dtype, batch=len(values))
+    ws = W.stack_weights(shape, 500 + hd, random_ln=True, std=0.03)
+    stored = W.to_bf16_values if dtype == "bf16" else lambda v: np.asarray(v, np.float32)
+    ws[0]["w_qkv"][:d] = 0.0
+    ws[0]["b_qkv"][:d] = 0.0
+    ws[0]["b_qkv"][0:d:hd] = 8.0
+    xt = W.template_hidden(shape, 500 + hd)
+    kv = np.stack([W.synthetic_kv_cache(shape, 500 + hd, 0)])
+    keys = np.concatenate([np.arange(64 * t, 64 * t + 64) for t in far])
+    for b, v in enumerate(values):
+        if v is not None:
+            # two values, so that the large positive ones are told apart (the weights of the lower are 0)
+            kv[0, b, keys, 0, 0:d:hd] = v
+            kv[0, b, keys[1::2], 0, 0:d:hd] = v if np.isinf(v) else stored(np.float32([0.9 * v]))
+    kv[0, :, :, 0] = np.where(np.isfinite(kv[0, :, :, 0]), stored(kv[0, :, :, 0]), kv[0, :, :, 0])
+    yc = W.synthetic_y_cache(shape, 500 + hd)
+    mask = np.zeros((len(values), shape.n_image), np.uint8)
+    mask[:, [129, 131, 134] if 1 in far else [64, 100, 127, 130]] = 1
+    x = W.edited_hidden(shape, 500 + hd, xt, mask)
+    y, _, _ = G.run_stack(shape, mask, x, kv, yc, ws, return_kv=False)
+    y_ref = oracle.masked_stack(x, mask, kv, yc, ws, shape, round_p=dtype == "bf16")
+    assert np.isfinite(y_ref).all()
+    for b, v in enumerate(values):
+        G.assert_close(y[b], y_ref[b], dtype, f"head_dim {hd}, keys of {v}", blocks=1, inp=x[b])
