@@ -164,14 +164,15 @@ def make_inputs(key, shape, n_masks, torch, W, cache="kv"):
 ROOT = os.path.dirname(os.path.abspath(__file__))
 
 # Kernel symbols (as rocprofv3 names them) of each bench kernel class: the GEMM
-# classes are told apart by their epilogue template argument (1 residual:
-# out and down projections alike, 2 GELU, 3 QKV split).
+# classes are told apart by their epilogue template argument (1 residual of the
+# attention output, 2 GELU, 3 QKV split, 4 residual of the MLP), the last of
+# either main loop's.
 FAMILY = {
-    "attention": (r"attention_dma_kernel<(\d+), 2>", "paper_2505_20600_amd/csrc/attention.hip"),
-    "gemm_up": (r"gemm_dl_kernel<\d+, \d+, \d, 2>", "paper_2505_20600_amd/csrc/gemm.hip"),
-    "gemm_qkv": (r"gemm_dl_kernel<\d+, \d+, \d, 3>", "paper_2505_20600_amd/csrc/gemm.hip"),
-    "gemm_out": (r"gemm_dl_kernel<\d+, \d+, \d, 1>", "paper_2505_20600_amd/csrc/gemm.hip"),
-    "gemm_down": (r"gemm_dl_kernel<\d+, \d+, \d, 4>", "paper_2505_20600_amd/csrc/gemm.hip"),
+    "attention": (r"attention_dma_kernel<\d+>", "paper_2505_20600_amd/csrc/attention.hip"),
+    "gemm_up": (r"gemm_(dl_kernel<\d+, \d+, \d|pp_kernel<\d+), 2>", "paper_2505_20600_amd/csrc/gemm.hip"),
+    "gemm_qkv": (r"gemm_(dl_kernel<\d+, \d+, \d|pp_kernel<\d+), 3>", "paper_2505_20600_amd/csrc/gemm.hip"),
+    "gemm_out": (r"gemm_(dl_kernel<\d+, \d+, \d|pp_kernel<\d+), 1>", "paper_2505_20600_amd/csrc/gemm.hip"),
+    "gemm_down": (r"gemm_(dl_kernel<\d+, \d+, \d|pp_kernel<\d+), 4>", "paper_2505_20600_amd/csrc/gemm.hip"),
     "gather": (r"::gather_kernel", "paper_2505_20600_amd/csrc/rows.hip"),
     "scatter": (r"::(scatter_masked|merge)_kernel", "paper_2505_20600_amd/csrc/rows.hip"),
 }
@@ -250,9 +251,11 @@ def summarize_trace(args):
         return
     rx = re.compile(FAMILY[args.family][0])
     fam = [r for r in rows if rx.search(r["Kernel_Name"])]
+    if not fam:
+        raise SystemExit(f"no dispatch of family {args.family} ({FAMILY[args.family][0]}) in the trace")
     fus = sum((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in fam)
     print(f"family {args.family} ({FAMILY[args.family][0]}): {len(fam)} launches, {fus / 1e3:.3f} ms, "
-          f"{fus / max(1, len(fam)):.2f} us per launch")
+          f"{fus / len(fam):.2f} us per launch")
     for path in args.counters:
         vals = {}
         for r in _window(_read_csv(path)):
@@ -268,11 +271,15 @@ def summarize_trace(args):
         if window:
             rr = _window(rr)
         vals = [float(r["Counter_Value"]) for r in rr if rx.search(r["Kernel_Name"])]
-        return sum(vals) / max(1, len(vals)), len(vals)
+        if not vals:
+            raise SystemExit(f"no dispatch of family {args.family} in {path}")
+        return sum(vals) / len(vals), len(vals)
 
     def copy_kib(path):
         vals = [float(r["Counter_Value"]) for r in _read_csv(path) if "copy" in r["Kernel_Name"].lower()]
-        return sum(vals) / max(1, len(vals))
+        if not vals:
+            raise SystemExit(f"no copy dispatch in {path}")
+        return sum(vals) / len(vals)
 
     fetch, nf = per_dispatch(args.pmc_fetch)
     write, nw = per_dispatch(args.pmc_write)
