@@ -16,7 +16,7 @@
 // the working K/V (the K/V cache of Fig. 7 with the masked rows replaced).
 //
 // bf16 tiles: BM x BN from 64 x 64 to 256 x 256, operands copied global ->
-// LDS without staging registers into 2-8 stages of 64-deep K steps, the 256 x
+// LDS without staging registers into 2-4 stages of 64-deep K steps, the 256 x
 // 256 and 256 x 192 ones refilled region by region (gemm_pp_kernel); fp32:
 // 64 x 64 or 32 x 32 tiles through registers, double-buffered. The host picks tile,
 // stage count and K split from a step-time table measured on MI355X; split
@@ -380,7 +380,7 @@ __device__ __forceinline__ void wait_stages(int left) {
 
 template <int BM, int BN, int S, int EPI>
 __global__ __launch_bounds__(kWave * dl_waves(BM, BN)) void gemm_dl_kernel(GemmDesc g) {
-    static_assert(S >= 2 && S <= 8, "stages");
+    static_assert(S >= 2 && S <= 4, "stages");
     constexpr int NW = dl_waves(BM, BN);
     constexpr int WM = 2, WN = NW / 2;          // wave grid: WM along m, WN along n
     using E = Elt<bf16_t>;
@@ -807,79 +807,93 @@ hipError_t launch_reduce(const GemmDesc& g, hipStream_t s) {
 
 }  // namespace
 
-// Tile and stage choice from a measured cost model. A launch whose busiest
-// CU holds n workgroups of a tile and stage count costs about
-// steps x a(n) + b(n) us: a(n) per 64-deep K step of the whole grid, b(n) the
-// per-tile work outside the K loop (prologue, epilogue, stores). Both come
-// from timing grids of n x 256 tiles (16 tile columns, GELU epilogue) at
-// K = 1024 and K = 4096 on MI355X with the direct-to-LDS main loop; between
-// the measured n the model interpolates linearly, past n = 48 it scales with n.
-// Split-K multiplies the groups, divides the steps and adds the
-// partial-sum pass.
+// Tile and stage choice from a measured cost model. A launch of g workgroups of a tile
+// and stage count costs about steps x a(g) + b(g) us: a(g) per 64-deep K step of the
+// whole grid, b(g) the work outside the K loop (prologue, epilogue, stores). Split-K
+// multiplies the groups, divides the steps and adds the partial-sum pass. a, b and the
+// pass's price are a least-squares fit (relative errors, non-negative) to 50000
+// measured launches on MI355X: 1220 shapes of 16 to 16384 rows, the four projections of
+// models 64 to 4096 wide, each over the tiles, stages and splits within twice the best
+// one's estimate, in graphs of launches whose operands rotate over 300 MB. Times of one
+// operand set, from L2, had misled the choice: 4096x1024x4096 128x128 tiles at 65 us
+// instead of 128x64 at 44, 512x1024x1024 a split in four at 12.7 instead of none at 8.1.
+// Over those shapes the choice is 1.3% slower than the best measured one (geometric
+// mean, worst 31%), against 7.5% (72%) with that table.
 namespace {
-constexpr int kCostN = 13;
-constexpr int kCostAt[kCostN] = {1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 24, 32, 48};
+constexpr int kCostN = 15;
+// g / 256 up to one workgroup per CU, the busiest CU's workgroups beyond (linear
+// between these, in proportion past the last)
+constexpr double kCostAt[kCostN] = {0.25, 0.5, 1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 24, 32, 48};
 struct TileCost {
     int bm, bn, stages;
-    double step[kCostN];   // a(n), us per K step
-    double tile[kCostN];   // b(n), us per launch
+    double step[kCostN];   // a, us per K step
+    double tile[kCostN];   // b, us per launch
 };
 constexpr TileCost kCost[] = {
-    {256, 256, 2, {1.375, 2.743, 4.416, 5.740, 7.350, 9.060, 10.388, 11.957, 17.533, 22.925, 35.281, 46.688, 70.811},
-     {21.5, 31.0, 36.3, 50.1, 60.2, 64.9, 79.3, 89.5, 143.2, 198.6, 264.0, 353.8, 526.3}},
-    {256, 192, 2, {1.141, 2.197, 3.304, 4.299, 5.524, 6.877, 8.098, 9.257, 13.871, 18.383, 27.482, 36.714, 56.485},
-     {12.1, 22.9, 32.1, 44.0, 50.5, 55.3, 62.8, 70.3, 111.7, 148.4, 226.9, 298.1, 389.5}},
-    {192, 192, 2, {0.901, 1.914, 2.792, 3.900, 4.818, 5.552, 6.819, 7.829, 12.209, 16.197, 24.192, 32.866, 49.133},
-     {11.7, 14.7, 23.9, 27.3, 32.3, 43.5, 45.1, 48.3, 65.8, 91.1, 166.5, 215.0, 318.7}},
-    {192, 192, 3, {0.881, 1.840, 2.742, 3.685, 4.651, 5.581, 6.744, 7.565, 11.651, 15.441, 22.846, 30.906, 47.177},
-     {10.0, 17.0, 24.0, 32.0, 37.1, 43.4, 45.9, 55.0, 75.6, 107.4, 166.0, 202.8, 299.5}},
-    {256, 128, 2, {0.913, 1.865, 2.801, 3.708, 4.650, 5.657, 6.809, 7.727, 12.096, 16.253, 23.475, 31.480, 47.090},
-     {12.3, 16.7, 22.9, 30.1, 36.1, 41.2, 43.9, 53.0, 68.4, 86.9, 165.2, 217.0, 306.1}},
-    {256, 128, 3, {0.966, 1.940, 2.922, 3.918, 4.875, 5.886, 7.145, 7.890, 12.215, 16.256, 24.130, 32.520, 48.522},
-     {10.6, 16.8, 23.2, 29.0, 36.0, 41.4, 43.5, 53.8, 73.0, 96.0, 159.0, 204.9, 298.0}},
-    {128, 128, 2, {0.619, 0.878, 1.364, 1.707, 2.324, 2.633, 3.180, 3.607, 5.519, 7.826, 11.631, 15.276, 22.946},
-     {5.7, 8.3, 11.6, 13.7, 15.0, 19.2, 18.3, 21.9, 31.7, 32.2, 51.1, 87.0, 132.7}},
-    {128, 128, 3, {0.610, 1.169, 1.755, 2.351, 2.939, 3.532, 4.093, 4.691, 7.031, 9.609, 14.368, 19.240, 28.278},
-     {7.4, 10.8, 13.0, 16.2, 19.5, 22.6, 27.0, 30.2, 43.8, 54.6, 80.1, 117.4, 184.2}},
-    {128, 128, 4, {0.576, 1.166, 1.721, 2.323, 2.908, 3.438, 4.070, 4.713, 6.874, 9.469, 14.181, 18.998, 27.628},
-     {6.5, 9.9, 14.4, 16.9, 20.0, 25.6, 26.8, 29.8, 48.2, 57.1, 84.6, 124.4, 200.9}},
-    {128, 64, 2, {0.577, 0.600, 0.834, 1.228, 1.420, 1.712, 2.053, 2.248, 3.419, 5.051, 8.088, 10.932, 15.954},
-     {1.0, 4.4, 6.6, 6.7, 6.7, 10.4, 8.2, 9.9, 15.8, 11.8, 7.4, 7.7, 44.6}},
-    {128, 64, 3, {0.417, 0.580, 0.949, 1.176, 1.495, 1.731, 2.141, 2.413, 3.539, 5.497, 8.522, 11.715, 16.886},
-     {4.9, 5.6, 7.0, 7.0, 9.5, 12.7, 10.7, 13.2, 19.8, 12.9, 11.5, 14.2, 51.9}},
-    {128, 64, 4, {0.404, 0.766, 1.160, 1.534, 1.937, 2.303, 2.695, 3.091, 4.640, 6.455, 9.913, 13.397, 18.917},
-     {4.8, 7.5, 8.9, 11.2, 13.3, 15.6, 17.6, 19.6, 28.3, 32.7, 44.5, 57.7, 121.9}},
-    {64, 128, 2, {0.577, 0.600, 0.824, 1.204, 1.385, 1.639, 2.037, 2.176, 3.415, 4.409, 7.119, 9.995, 15.349},
-     {1.6, 5.4, 7.5, 7.7, 7.9, 11.5, 9.3, 13.3, 14.5, 19.7, 27.2, 22.1, 35.4}},
-    {64, 128, 3, {0.428, 0.626, 0.973, 1.192, 1.534, 1.825, 2.178, 2.453, 3.654, 4.817, 7.760, 10.961, 16.477},
-     {4.9, 4.9, 7.4, 7.6, 8.7, 9.6, 8.9, 11.2, 17.9, 24.8, 25.7, 24.6, 37.5}},
-    {64, 128, 4, {0.420, 0.815, 1.232, 1.642, 2.063, 2.477, 2.882, 3.293, 4.927, 6.592, 10.017, 13.490, 19.986},
-     {4.4, 7.1, 8.9, 11.2, 13.0, 15.1, 17.5, 19.9, 28.9, 37.3, 52.6, 67.4, 113.8}},
-    {64, 64, 2, {0.491, 0.505, 0.558, 0.688, 1.042, 1.125, 1.254, 1.334, 2.208, 3.227, 4.877, 7.753, 14.886},
-     {0.4, 1.4, 3.5, 4.4, 5.3, 4.5, 5.3, 8.7, 12.7, 9.9, 10.6, 0.4, 0.0}},
-    {64, 64, 3, {0.295, 0.400, 0.586, 0.750, 0.871, 1.145, 1.253, 1.426, 2.234, 2.915, 4.538, 6.976, 11.249},
-     {3.8, 3.2, 3.3, 4.4, 6.1, 4.7, 7.6, 7.1, 8.6, 9.4, 11.8, 1.4, 0.0}},
-    {64, 64, 4, {0.277, 0.373, 0.623, 0.705, 0.995, 1.099, 1.327, 1.473, 2.238, 2.991, 4.483, 6.954, 10.693},
-     {3.9, 3.4, 5.0, 6.2, 5.6, 7.7, 7.8, 8.8, 12.2, 14.8, 21.6, 11.5, 14.2}},
+    {256, 256, 2, {1.153, 1.113, 1.467, 2.768, 4.323, 5.256, 6.176, 8.451, 9.427, 11.142, 17.706, 22.925, 35.281, 46.687, 70.807},
+     {9.3, 9.8, 10.3, 17.0, 27.9, 53.9, 81.8, 69.3, 102.1, 96.0, 149.2, 198.3, 263.2, 351.8, 519.9}},
+    {256, 192, 2, {0.962, 0.917, 1.064, 2.128, 3.353, 4.762, 5.279, 6.194, 7.153, 8.568, 13.287, 18.546, 27.009, 36.713, 56.483},
+     {7.6, 8.9, 9.1, 15.9, 24.4, 25.9, 47.4, 65.5, 79.5, 81.1, 121.6, 150.9, 224.4, 296.9, 386.9}},
+    {192, 192, 2, {1.024, 1.023, 1.037, 2.018, 3.010, 4.215, 4.740, 6.233, 7.313, 8.058, 12.272, 16.655, 24.696, 32.866, 49.132},
+     {5.2, 6.4, 7.2, 11.1, 15.9, 18.0, 30.4, 26.5, 30.3, 49.4, 68.2, 90.5, 165.5, 214.6, 317.3}},
+    {192, 192, 3, {0.791, 0.793, 0.874, 1.756, 2.731, 3.868, 4.521, 5.751, 6.421, 6.938, 11.042, 15.018, 22.788, 30.906, 47.176},
+     {7.3, 7.7, 7.2, 11.6, 17.1, 21.0, 31.0, 31.8, 43.0, 63.3, 75.0, 110.5, 164.9, 202.4, 298.3}},
+    {256, 128, 2, {1.008, 0.993, 1.013, 1.969, 3.136, 4.120, 5.272, 6.122, 6.325, 6.936, 12.015, 16.492, 24.488, 31.480, 47.089},
+     {7.6, 7.0, 7.9, 13.0, 16.6, 27.0, 27.3, 37.4, 49.8, 76.0, 84.4, 94.1, 171.7, 216.5, 304.8}},
+    {256, 128, 3, {1.378, 1.185, 1.079, 2.449, 3.395, 4.570, 5.681, 6.230, 6.361, 7.366, 11.383, 16.072, 24.341, 32.520, 48.521},
+     {5.7, 6.2, 8.2, 10.0, 14.4, 21.5, 21.2, 35.0, 48.0, 67.3, 95.7, 107.1, 160.8, 204.5, 296.8}},
+    {128, 128, 2, {0.706, 0.709, 0.762, 0.876, 1.582, 1.828, 2.446, 2.862, 3.390, 3.724, 6.013, 7.377, 11.409, 15.064, 24.211},
+     {3.8, 4.6, 5.4, 6.4, 8.2, 10.1, 10.7, 11.9, 10.8, 15.6, 11.8, 34.1, 65.3, 98.9, 139.8}},
+    {128, 128, 3, {0.834, 0.730, 0.671, 1.514, 2.280, 2.948, 3.645, 4.361, 4.965, 5.616, 8.400, 9.217, 14.150, 18.688, 28.924},
+     {4.4, 4.6, 5.5, 6.3, 8.3, 12.4, 10.3, 11.2, 14.0, 16.1, 16.4, 54.3, 86.2, 120.2, 188.0}},
+    {128, 128, 4, {0.856, 0.732, 0.657, 1.512, 2.264, 2.935, 3.616, 4.306, 4.924, 5.574, 8.309, 9.093, 13.996, 18.517, 28.601},
+     {3.7, 4.6, 5.8, 6.6, 8.6, 12.6, 10.5, 11.7, 13.7, 15.9, 15.6, 56.6, 91.7, 128.1, 206.9}},
+    {128, 64, 2, {0.465, 0.558, 0.577, 0.672, 0.870, 1.418, 1.469, 1.772, 2.096, 2.303, 3.488, 4.598, 7.454, 10.587, 15.275},
+     {3.2, 3.6, 4.0, 4.2, 5.3, 5.7, 6.5, 7.7, 7.9, 9.9, 10.4, 12.1, 7.9, 8.3, 45.6}},
+    {128, 64, 3, {0.500, 0.522, 0.488, 0.699, 1.056, 1.380, 1.817, 2.057, 2.172, 2.700, 3.693, 5.293, 8.321, 11.032, 16.383},
+     {3.1, 3.6, 4.1, 4.3, 5.9, 5.7, 5.7, 8.0, 9.2, 8.9, 13.3, 13.6, 9.6, 15.3, 50.4}},
+    {128, 64, 4, {0.488, 0.511, 0.460, 0.997, 1.665, 2.318, 2.809, 3.158, 3.484, 4.170, 5.805, 7.373, 9.927, 12.763, 18.744},
+     {3.1, 3.6, 4.3, 5.6, 5.1, 5.1, 6.4, 9.1, 10.9, 9.8, 14.0, 20.8, 37.9, 60.3, 123.2}},
+    {64, 128, 2, {0.508, 0.567, 0.586, 0.677, 0.888, 1.385, 1.485, 1.758, 2.134, 2.298, 3.387, 4.695, 7.017, 10.186, 15.405},
+     {3.3, 3.7, 4.4, 4.6, 5.8, 6.3, 7.4, 9.9, 8.3, 11.0, 13.5, 13.2, 23.4, 25.8, 37.7}},
+    {64, 128, 3, {0.469, 0.445, 0.449, 0.619, 1.036, 1.319, 1.651, 1.895, 2.233, 2.532, 3.711, 4.980, 7.996, 10.714, 16.323},
+     {3.3, 4.0, 4.6, 5.1, 6.2, 7.0, 7.9, 10.7, 9.9, 12.6, 15.6, 19.5, 22.3, 26.2, 39.0}},
+    {64, 128, 4, {0.456, 0.438, 0.439, 0.832, 1.277, 1.711, 2.136, 2.529, 2.981, 3.349, 5.198, 6.765, 10.058, 13.569, 20.259},
+     {3.4, 4.1, 4.8, 6.5, 7.5, 9.0, 11.2, 13.7, 14.9, 19.1, 24.5, 34.9, 51.0, 70.6, 116.1}},
+    {64, 64, 2, {0.405, 0.514, 0.495, 0.505, 0.603, 0.748, 1.167, 1.189, 1.452, 1.531, 2.632, 3.470, 5.288, 7.679, 11.794},
+     {2.7, 2.9, 3.2, 3.7, 4.4, 5.0, 5.3, 6.6, 4.9, 7.5, 9.6, 13.6, 11.4, 1.0, 1.0}},
+    {64, 64, 3, {0.309, 0.318, 0.332, 0.401, 0.606, 0.798, 0.999, 1.170, 1.450, 1.513, 2.371, 3.103, 4.769, 7.022, 10.417},
+     {2.9, 3.2, 3.5, 3.9, 4.6, 5.1, 4.9, 6.3, 4.5, 7.2, 9.1, 12.2, 10.7, 1.5, 1.0}},
+    {64, 64, 4, {0.297, 0.299, 0.297, 0.408, 0.655, 0.814, 1.032, 1.174, 1.499, 1.588, 2.386, 3.198, 4.897, 6.722, 10.247},
+     {3.0, 3.2, 3.6, 4.1, 5.1, 5.4, 5.8, 7.2, 5.5, 8.4, 11.2, 13.3, 15.4, 12.7, 14.6}},
 };
 
-double interp(const double* v, long n) {
-    if (n <= kCostAt[0]) return v[0];
+double interp(const double* v, double x) {
+    if (x <= kCostAt[0]) return v[0];
     for (int i = 1; i < kCostN; ++i)
-        if (n <= kCostAt[i])
-            return v[i - 1] + (v[i] - v[i - 1]) * (double)(n - kCostAt[i - 1]) / (kCostAt[i] - kCostAt[i - 1]);
-    return v[kCostN - 1] * (double)n / kCostAt[kCostN - 1];
+        if (x <= kCostAt[i])
+            return v[i - 1] + (v[i] - v[i - 1]) * (x - kCostAt[i - 1]) / (kCostAt[i] - kCostAt[i - 1]);
+    return v[kCostN - 1] * x / kCostAt[kCostN - 1];
 }
+
+// Modelled time of `steps` K steps of an M x N product in `ks` K ranges, without the
+// partial-sum pass.
+double tile_us(const TileCost& c, int M, int N, int steps, int ks) {
+    const long groups = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * ks;
+    const double x = groups <= kCUs ? (double)groups / kCUs : (double)((groups + kCUs - 1) / kCUs);
+    return ((steps + ks - 1) / ks) * interp(c.step, x) + interp(c.tile, x);
+}
+
 // The same for float32, per 32-deep step (bias epilogue, K = 256 and 1024). 32 x 32
 // tiles are the quicker ones while the launch is short of workgroups (a step waits
 // for its loads: 0.36 us against 0.76 at n = 1), 64 x 64 read half as much per
 // product. Before, 64 x 64 and no K split: 205x256x1024 26 -> 8 us, 205x768x256
 // 9.3 -> 5.1, 800x512x2048 50 -> 30, 3000x512x2048 82 -> 67.
 constexpr TileCost kCostF32[] = {
-    {64, 64, 2, {0.76, 1.34, 1.85, 2.43, 2.95, 3.45, 4.05, 4.62, 6.63, 8.90, 13.0, 17.1, 25.6},
-     {4.0, 5.1, 6.8, 7.0, 10.0, 12.0, 10.5, 9.5, 13.8, 14.6, 23.0, 32.0, 48.0}},
-    {32, 32, 2, {0.356, 0.483, 0.693, 0.882, 1.07, 1.26, 1.44, 1.63, 2.31, 3.15, 4.50, 5.74, 8.60},
-     {2.35, 2.45, 2.78, 2.92, 3.2, 3.5, 3.9, 4.3, 6.3, 6.5, 8.0, 10.2, 15.0}},
+    {64, 64, 2, {0.76, 0.76, 0.76, 1.34, 1.85, 2.43, 2.95, 3.45, 4.05, 4.62, 6.63, 8.90, 13.0, 17.1, 25.6},
+     {4.0, 4.0, 4.0, 5.1, 6.8, 7.0, 10.0, 12.0, 10.5, 9.5, 13.8, 14.6, 23.0, 32.0, 48.0}},
+    {32, 32, 2, {0.356, 0.356, 0.356, 0.483, 0.693, 0.882, 1.07, 1.26, 1.44, 1.63, 2.31, 3.15, 4.50, 5.74, 8.60},
+     {2.35, 2.35, 2.35, 2.45, 2.78, 2.92, 3.2, 3.5, 3.9, 4.3, 6.3, 6.5, 8.0, 10.2, 15.0}},
 };
 
 GemmPlan plan_f32(int M, int N, int K, size_t part_capacity_floats) {
@@ -887,12 +901,9 @@ GemmPlan plan_f32(int M, int N, int K, size_t part_capacity_floats) {
     const int steps = K / 32;
     double best = 1e30;
     for (const TileCost& c : kCostF32) {
-        const long grp = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
         for (int ks = 1; ks <= 8 && ks <= steps; ++ks) {
             if (ks > 1 && (size_t)ks * M * N > part_capacity_floats) break;
-            const int per = (steps + ks - 1) / ks;
-            const long n = (grp * ks + kCUs - 1) / kCUs;
-            double us = per * interp(c.step, n) + interp(c.tile, n);
+            double us = tile_us(c, M, N, steps, ks);
             // partial sums: 2.1 us at two planes of 205 x 256, 4.0 at eight
             if (ks > 1) us += 2.0 + 0.25 * ks + ((double)ks * 4 + 4) * M * N / 4.0e6;
             if (us < best * 0.97) {
@@ -905,7 +916,7 @@ GemmPlan plan_f32(int M, int N, int K, size_t part_capacity_floats) {
 }
 }  // namespace
 
-GemmPlan plan_gemm(int dtype, int M, int N, int K, size_t part_capacity_floats) {
+GemmPlan plan_gemm(int dtype, int M, int N, int K, size_t part_capacity_floats, bool ln_sum) {
     GemmPlan p{64, 64, 1, 2};
     if (dtype != kBF16) return plan_f32(M, N, K, part_capacity_floats);
     const int steps = K / 64;
@@ -915,29 +926,19 @@ GemmPlan plan_gemm(int dtype, int M, int N, int K, size_t part_capacity_floats) 
         return v ? std::max(0.0, std::atof(v)) : 1.0;
     }();
     for (const TileCost& c : kCost) {
-        const long grp = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
         for (int ks = 1; ks <= 8 && ks <= steps; ++ks) {
             if (ks > 1 && (size_t)ks * M * N > part_capacity_floats) break;
-            const int per = (steps + ks - 1) / ks;
-            const long n = (grp * ks + kCUs - 1) / kCUs;
-            double us = per * interp(c.step, n) + interp(c.tile, n);
-            // partial sums: ks float planes read, one bf16 plane written, ~4 TB/s, + a launch
-            if (ks > 1) us += split_scale * (2.0 + ((double)ks * 4 + 2) * M * N / 4.0e6);
-            if (us < best * 0.97) {   // prefer the earlier (larger, unsplit) choice on near-ties
+            double us = tile_us(c, M, N, steps, ks);
+            // partial sums: ks float planes read, one bf16 plane written, ~4 TB/s, + a launch;
+            // as part of the LayerNorm that would follow anyway 2 us less (block of 205 rows
+            // at d 768 54.3 -> 53.0 us; 4 us less: 12 blocks of 1229 rows 1092 -> 1103)
+            if (ks > 1) us += split_scale * ((ln_sum ? -0.5 : 1.54) + 0.27 * ks + ((double)ks * 4 + 2) * M * N / 4.0e6);
+            if (us < best) {
                 best = us;
                 p = GemmPlan{c.bm, c.bn, ks, c.stages};
             }
         }
     }
-    // At most one workgroup per CU: the rest of its LDS holds more stages. Its K step
-    // waits for the operand stream (16 KB of a 64 x 64 tile in 0.28 us at four stages,
-    // about 26 B per clock and CU), which is deeper with more copies in flight. With
-    // two workgroups on a CU the extra stages would keep the second one out. Together
-    // with the waits of the last steps, which leave the copies still needed in flight:
-    // block of 205 rows at d 768 58.8 -> 55.8 us, 12 blocks of 1229 rows 1141 -> 1094,
-    // other sizes even; outputs bit-identical.
-    if (p.bm * p.bn <= 128 * 64 && (long)((M + p.bm - 1) / p.bm) * ((N + p.bn - 1) / p.bn) * p.ksplit <= kCUs)
-        p.stages = p.bm * p.bn == 64 * 64 ? 8 : 6;
     if (const char* f = std::getenv("MS_GEMM_TILE")) {   // tuning override "BMxBN"
         int bm = 0, bn = 0;
         if (std::sscanf(f, "%dx%d", &bm, &bn) == 2) {
@@ -951,7 +952,7 @@ GemmPlan plan_gemm(int dtype, int M, int N, int K, size_t part_capacity_floats) 
 // Largest stage count whose LDS fits next to nothing else (160 KB per CU).
 int max_stages(int bm, int bn) {
     const int per = (bm + bn) * 64 * 2;
-    return std::min(8, (160 * 1024) / per);
+    return std::min(4, (160 * 1024) / per);
 }
 
 hipError_t launch_gemm(int dtype, GemmDesc& g, hipStream_t s) {
@@ -996,10 +997,10 @@ hipError_t launch_gemm(int dtype, GemmDesc& g, hipStream_t s) {
     if (g.bm == 128 && g.bn == 128)
         return st >= 4 ? launch_dl<128, 128, 4>(g, s) : st == 3 ? launch_dl<128, 128, 3>(g, s) : launch_dl<128, 128, 2>(g, s);
     if (g.bm == 128 && g.bn == 64)
-        return st >= 6 ? launch_dl<128, 64, 6>(g, s) : st >= 4 ? launch_dl<128, 64, 4>(g, s) : st == 3 ? launch_dl<128, 64, 3>(g, s) : launch_dl<128, 64, 2>(g, s);
+        return st >= 4 ? launch_dl<128, 64, 4>(g, s) : st == 3 ? launch_dl<128, 64, 3>(g, s) : launch_dl<128, 64, 2>(g, s);
     if (g.bm == 64 && g.bn == 128)
-        return st >= 6 ? launch_dl<64, 128, 6>(g, s) : st >= 4 ? launch_dl<64, 128, 4>(g, s) : st == 3 ? launch_dl<64, 128, 3>(g, s) : launch_dl<64, 128, 2>(g, s);
-    return st >= 8 ? launch_dl<64, 64, 8>(g, s) : st >= 4 ? launch_dl<64, 64, 4>(g, s) : st == 3 ? launch_dl<64, 64, 3>(g, s) : launch_dl<64, 64, 2>(g, s);
+        return st >= 4 ? launch_dl<64, 128, 4>(g, s) : st == 3 ? launch_dl<64, 128, 3>(g, s) : launch_dl<64, 128, 2>(g, s);
+    return st >= 4 ? launch_dl<64, 64, 4>(g, s) : st == 3 ? launch_dl<64, 64, 3>(g, s) : launch_dl<64, 64, 2>(g, s);
 }
 
 hipError_t launch_gemm_reduce(int dtype, const GemmDesc& g, hipStream_t s) {

@@ -81,8 +81,9 @@ struct GemmPlan {
 // the CUs (e.g. 2048 text rows ahead of a LayerNorm) get one at every width.
 constexpr size_t gemm_part_floats(size_t d_model) { return size_t(5461) * d_model; }
 
-// Tile shape and K split for an M x N x K product on 256 CUs.
-GemmPlan plan_gemm(int dtype, int M, int N, int K, size_t part_capacity_floats);
+// Tile shape and K split for an M x N x K product on 256 CUs. `ln_sum`: a LayerNorm
+// follows, whose launch would take over the sum of a K split.
+GemmPlan plan_gemm(int dtype, int M, int N, int K, size_t part_capacity_floats, bool ln_sum = false);
 
 // a4/a5/a7/a8/a9: out = epi(A W^T + bias); with ksplit > 1 only the partials
 // (launch_gemm_reduce applies the epilogue). launch_gemm sets g.kchunk/ksplit.

@@ -461,7 +461,10 @@ struct LnAfter {
 // fused into the split-K sum when the plan splits K (bias + residual
 // epilogue only), else a LayerNorm launch of its own.
 hipError_t run_gemm(ms_step* s, ms::GemmDesc& g, int cls, hipStream_t st, const LnAfter* ln = nullptr) {
-    const ms::GemmPlan p = ms::plan_gemm(s->desc.dtype, g.M, g.N, g.K, ms::gemm_part_floats(s->d));
+    // The plan of a shape is the same with and without a following block, so that a stack
+    // and its blocks called one by one give the same bits: only LayerNorm 2 counts.
+    const bool ln2 = g.epilogue == ms::kEpiBiasResid;
+    const ms::GemmPlan p = ms::plan_gemm(s->desc.dtype, g.M, g.N, g.K, ms::gemm_part_floats(s->d), ln2);
     g.bm = p.bm;
     g.bn = p.bn;
     g.stages = p.stages;

@@ -15,7 +15,7 @@ TILES = [(256, 256), (256, 192), (192, 192), (256, 128), (128, 128), (128, 64), 
 # every deeper stage variant the library builds (tile, stages); the forced-tile
 # tests above run two stages
 STAGED = [((192, 192), 3), ((256, 128), 3), ((128, 128), 3), ((128, 128), 4), ((128, 64), 3), ((128, 64), 4),
-          ((64, 128), 3), ((64, 128), 4), ((64, 64), 3), ((64, 64), 4), ((128, 64), 6), ((64, 128), 6), ((64, 64), 8)]
+          ((64, 128), 3), ((64, 128), 4), ((64, 64), 3), ((64, 64), 4)]
 
 
 def _ref(A, W, b, R, epi):
@@ -127,6 +127,46 @@ def test_gelu_of_huge_and_infinite_values(dtype, tile, ksplit):
     assert bool(((out.float() - want).nan_to_num(0.0).abs() <= 2 ** -8 * want.abs().nan_to_num(0.0, 0.0)).all())
     assert torch.equal(out.isnan(), want.isnan())
     assert torch.equal(out.isinf(), want.isinf())
+
+
+@pytest.mark.parametrize("M,N,K", [(4096, 1024, 4096), (512, 1024, 1024), (2900, 1152, 4608), (205, 1024, 4096)])
+def test_planned_launch_is_near_the_best_forced_one(M, N, K):
+    """The planner's tile and split against every tile with one, two and four K ranges, in graphs of launches whose
+    operands rotate (as layers' weights do): at most 30% behind. Before the cost table was fitted to such launches
+    the first three were 47 to 62% behind."""
+    sets = max(2, min(12, int(3e8 / (2 * (M * K + N * K + M * N)))))
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    A = [torch.randn(M, K, device=DEV, generator=g).bfloat16() for _ in range(sets)]
+    W = [(torch.randn(N, K, device=DEV, generator=g) * 0.05).bfloat16() for _ in range(sets)]
+    b = torch.zeros(N, device=DEV, dtype=torch.bfloat16)
+    out = [torch.empty(M, N, device=DEV, dtype=torch.bfloat16) for _ in range(sets)]
+    ws = torch.empty(8 * M * N * 4, device=DEV, dtype=torch.uint8)
+
+    def us(**kw):
+        def go(i):
+            MS.ms_linear(A[i % sets], W[i % sets], b, out[i % sets], resid=out[0], epilogue=MS.MS_EPI_BIAS_RESID,
+                         workspace=ws, **kw)
+        go(0)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for i in range(24):
+                go(i)
+        times = []
+        for _ in range(6):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            graph.replay()
+            e1.record()
+            torch.cuda.synchronize()
+            times.append(e0.elapsed_time(e1) * 1000 / 24)
+        return min(times)
+
+    planned = us()
+    forced = {(t, k): us(tile=t, ksplit=k) for t in TILES for k in (1, 2, 4)}
+    best = min(forced, key=forced.get)
+    print(f"[plan] {M}x{N}x{K}: {planned:.1f} us, best forced {best} {forced[best]:.1f}")
+    assert planned <= 1.3 * forced[best]
 
 
 @pytest.mark.parametrize("ksplit", [2, 3, 5])
