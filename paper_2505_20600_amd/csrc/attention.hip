@@ -706,15 +706,19 @@ int f32_head_cols(int hd) { return hd <= 32 ? 32 : hd <= 48 ? 48 : 64; }
 // 16.1 us), 512 instead of 640 at 1024 rows of 16 heads of 72 (38.7 -> 36.0)
 // and no split at 16 requests of 10 to 60% of 1024 keys (26.2 -> 22.7).
 double attention_cost_us(int dtype, int base, int nsplit, int tps, int hd, int M, int d) {
-    // float32, measured the same way at head_dim 32, 40 and 64: a 64-key tile takes
-    // (0.030 + 0.036 k) us per padded column with k workgroups on a CU (the second
-    // term is the float32 matrix rate), a round 3.4 us + 0.8 per further workgroup.
+    // float32, the same terms from splits of 48 blocks at head_dim 32, 40 and 64: a 64-key
+    // tile takes (0.020 + 0.042 k) us per padded column with k workgroups on a CU (the
+    // second term is the float32 matrix rate), a round 2.0 us + 0.8 per further
+    // workgroup. The registers hold four workgroups per CU at 48 and 64 columns and five
+    // at 32, where rounds of eight come nearer the measured times (the next workgroups
+    // start as the first end). The planned split is 0.8% behind the best of these blocks
+    // (geometric mean, worst 4.7%; with rounds of eight, six and four 1.2%, 6.3%).
     // 205 rows of 4 heads of 64 over 1024 keys (16 workgroups unsplit) 67 -> 9 us
     // with the combine, 410 rows of 4 heads over 4096 keys 290 -> 36 us.
     if (dtype != kBF16) {
-        const int hdp = f32_head_cols(hd), per_cu = hdp == 32 ? 8 : hdp == 48 ? 6 : 4;
+        const int hdp = f32_head_cols(hd), per_cu = hdp == 32 ? 8 : 4;
         const long groups = (long)base * nsplit, slots = 256L * per_cu, rest = groups % slots;
-        auto round_us = [&](long k) { return 3.4 + 0.8 * (k - 1) + tps * hdp * (0.030 + 0.036 * k); };
+        auto round_us = [&](long k) { return 2.0 + 0.8 * (k - 1) + tps * hdp * (0.020 + 0.042 * k); };
         double us = (double)(groups / slots) * round_us(per_cu);
         if (rest) us += round_us((rest + 255) / 256);
         if (nsplit > 1) us += 2.5 + 0.1 * nsplit + (4.0 * nsplit + 4) * M * d / 6.0e6;
