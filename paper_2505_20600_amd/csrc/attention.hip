@@ -696,15 +696,18 @@ int f32_head_cols(int hd) { return hd <= 32 ? 32 : hd <= 48 ? 48 : 64; }
 }  // namespace
 
 // Split of the key range. Workgroups run in rounds of as many as the CUs hold
-// (set by the registers of each head_dim). Measured on MI355X over 1 to 24
-// ranges at head_dim 64, 72, 96 and 128: a round with k workgroups per CU takes
-// about 6 + 2.5 (k - 1) us to start and end plus, per 64-key tile, the tile's
-// MFMA count times 0.0115 + 0.0067 k us (12% more where an odd row length
-// leaves bank conflicts), and the combine a launch plus the partials' bytes at
-// ~6 TB/s. Against a fixed target of 640 workgroups the choice is 240 instead
-// of 528 at 205 rows of 12 heads over 4096 keys (attention and combine 20.0 ->
-// 16.1 us), 512 instead of 640 at 1024 rows of 16 heads of 72 (38.7 -> 36.0)
-// and no split at 16 requests of 10 to 60% of 1024 keys (26.2 -> 22.7).
+// (set by the registers of each head_dim). Fitted to forced splits of 176 blocks on
+// MI355X (1 to 32 ranges, head_dim 16 to 128, 52 to 2867 rows over 256 to 4096 keys): a
+// round with k workgroups per CU takes about 6 + 1.5 (k - 1) us to start and end plus,
+// per 64-key tile, the tile's MFMA count times 0.0115 + 0.0067 k us (12% more where an
+// odd row length leaves bank conflicts); the combine a launch, the partials' bytes at
+// ~6 TB/s and, past eight ranges, 3 us more (partials in chunks of eight, one after
+// the other). The planned split is 0.4% behind the best of these blocks (geometric mean,
+// worst 4.8%); with 2.5 (k - 1) and no price on more than eight ranges it was 1.5%
+// (18%): 230 rows of 3 heads of 128 over 2304 keys 47.1 -> 39.8 us.
+// Against a fixed target of 640 workgroups: no split at 16 requests of 10 to 60% of
+// 1024 keys (attention and combine 26.2 -> 22.7 us), 512 groups instead of 640 at 1024
+// rows of 16 heads of 72 (38.7 -> 36.0).
 double attention_cost_us(int dtype, int base, int nsplit, int tps, int hd, int M, int d) {
     // float32, the same terms from splits of 48 blocks at head_dim 32, 40 and 64: a 64-key
     // tile takes (0.020 + 0.042 k) us per padded column with k workgroups on a CU (the
@@ -727,11 +730,11 @@ double attention_cost_us(int dtype, int base, int nsplit, int tps, int hd, int M
     const int per_cu = hd <= 16 ? 5 : hd <= 48 ? 4 : hd <= 88 ? 3 : 2;
     const int mfmas = 8 * ((hd + 31) / 32) + 4 * ((hd + 15) / 16 + (hd % 16 == 0));
     const double unit = mfmas * (hd % 16 ? 1.12 : 1.0);
-    auto round_us = [&](long k) { return tps * unit * (0.0115 + 0.0067 * k) + 6.0 + 2.5 * (k - 1); };
+    auto round_us = [&](long k) { return tps * unit * (0.0115 + 0.0067 * k) + 6.0 + 1.5 * (k - 1); };
     const long groups = (long)base * nsplit, slots = 256L * per_cu, rest = groups % slots;
     double us = (double)(groups / slots) * round_us(per_cu);
     if (rest) us += round_us((rest + 255) / 256);
-    if (nsplit > 1) us += 2.5 + (4.0 * nsplit + 2) * M * d / 6.0e6;
+    if (nsplit > 1) us += 1.5 + 0.05 * nsplit + (nsplit > 8 ? 3.0 : 0.0) + (4.0 * nsplit + 2) * M * d / 6.0e6;
     return us;
 }
 
