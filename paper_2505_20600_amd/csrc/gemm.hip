@@ -101,7 +101,7 @@ __device__ __forceinline__ void epilogue_store(const GemmDesc& g, int m, int n, 
 // one row, so direct stores write 32-byte pieces of 16 rows. Against staging the
 // float32 tile, in two passes where it does not fit: 8547x3456x1152 (256x256
 // tiles, bias) 77.4 -> 67.8 us, 8547x4608x1152 (GELU) 127.3 -> 118.2 us.
-// Starts with a barrier; the caller has one before the LDS is written again.
+// Starts and ends with the workgroup past its last LDS read.
 template <int EPI, int BM, int BN, int WN, int SM, int SN>
 __device__ __forceinline__ void store_tile_bf16(const GemmDesc& g, void* smem, const f32x4_t (&acc)[SN][SM], int m0, int n0,
                                                 int tid, int wm, int wn) {
@@ -140,12 +140,11 @@ __device__ __forceinline__ void store_tile_bf16(const GemmDesc& g, void* smem, c
     __syncthreads();
 }
 
-// Outputs with a residual, and split-K partials: the float32 tile is staged in PASSES
+// Residual outputs and split-K partials: the float32 tile is staged in PASSES
 // passes (16-byte chunks XOR-swizzled by the row), each wave row's blocks spread
 // evenly over them; a lane then takes 8 columns of a row (16-byte residual loads
 // and stores; 8547x1152x1152 34.6 -> 34.1 us against 4 columns), of a partial 4
-// (32 bytes per lane: 1434x768x3072 in four ranges 18.2 -> 19.2 us). Each pass starts
-// with a barrier; the caller has one before the LDS is written again.
+// (32 bytes per lane: 1434x768x3072 in four ranges 18.2 -> 19.2 us). Starts and ends with the workgroup past its last LDS read.
 template <int EPI, int BM, int BN, int WN, int SM, int SN, int PASSES>
 __device__ __forceinline__ void store_tile_f32(const GemmDesc& g, void* smem, const f32x4_t (&acc)[SN][SM], int m0, int n0,
                                                int kz, int tid, int wm, int wn) {
@@ -153,7 +152,7 @@ __device__ __forceinline__ void store_tile_f32(const GemmDesc& g, void* smem, co
     constexpr int CPR = BN / 8, THREADS = 2 * WN * kWave, JP = SM / PASSES, RW = JP * 16;   // rows of a wave row per pass
     const int l16 = tid % 16, grp = tid % kWave / 16;
     float* const sc = static_cast<float*>(smem);
-    const bool wide = g.ldc % 8 == 0 && g.ldr % 8 == 0;   // 16-byte aligned rows
+    const bool wide = g.ldc % 8 == 0 && (!epi_resid(EPI) || g.ldr % 8 == 0) && (EPI != kEpiQKV || g.kvld % 8 == 0);
     __syncthreads();
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
@@ -168,7 +167,7 @@ __device__ __forceinline__ void store_tile_f32(const GemmDesc& g, void* smem, co
             }
         }
         __syncthreads();
-        if (!epi_resid(EPI) || g.ksplit > 1) {
+        if (g.ksplit > 1) {
             constexpr int CPF = BN / 4;
             for (int idx = tid; idx < 2 * RW * CPF; idx += THREADS) {
                 const int ml = idx / CPF, c = idx % CPF;
@@ -179,31 +178,38 @@ __device__ __forceinline__ void store_tile_f32(const GemmDesc& g, void* smem, co
             __syncthreads();
             continue;
         }
-        if constexpr (epi_resid(EPI)) {
-            for (int idx = tid; idx < 2 * RW * CPR; idx += THREADS) {
-                const int ml = idx / CPR, c = idx % CPR;
-                const int m = m0 + (ml / RW) * (BM / 2) + pass * RW + ml % RW, n = n0 + c * 8;
-                if (m >= g.M || n >= g.N) continue;
-                float v[8];
-                load4<float>(sc + ml * BN + (((2 * c) ^ (ml & 15)) * 4), v);
-                load4<float>(sc + ml * BN + (((2 * c + 1) ^ (ml & 15)) * 4), v + 4);
-                if (wide && n + 8 <= g.N) {
-                    const vec16 bw = ld16(static_cast<const bf16_t*>(g.bias) + n);
-                    const vec16 rw = ld16(static_cast<const bf16_t*>(g.R) + (long)m * g.ldr + n);
-                    vec16 ow;
+        for (int idx = tid; idx < 2 * RW * CPR; idx += THREADS) {
+            const int ml = idx / CPR, c = idx % CPR;
+            const int m = m0 + (ml / RW) * (BM / 2) + pass * RW + ml % RW, n = n0 + c * 8;
+            if (m >= g.M || n >= g.N) continue;
+            float v[8];
+            load4<float>(sc + ml * BN + (((2 * c) ^ (ml & 15)) * 4), v);
+            load4<float>(sc + ml * BN + (((2 * c + 1) ^ (ml & 15)) * 4), v + 4);
+            if (wide && n + 8 <= g.N) {
+                const vec16 bw = ld16(static_cast<const bf16_t*>(g.bias) + n);
+                vec16 rw = {{0u, 0u, 0u, 0u}}, ow;
+                if constexpr (epi_resid(EPI)) rw = ld16(static_cast<const bf16_t*>(g.R) + (long)m * g.ldr + n);
 #pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        v[2 * w] += __uint_as_float(bw.w[w] << 16);
-                        v[2 * w + 1] += __uint_as_float(bw.w[w] & 0xffff0000u);
-                        v[2 * w] += __uint_as_float(rw.w[w] << 16);
-                        v[2 * w + 1] += __uint_as_float(rw.w[w] & 0xffff0000u);
-                        ow.w[w] = pack_bf16x2(v[2 * w], v[2 * w + 1]);
+                for (int h = 0; h < 2; ++h) {
+                    float bv[4], rv[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const uint32_t wb = bw.w[2 * h + r / 2], wr = rw.w[2 * h + r / 2];
+                        bv[r] = __uint_as_float(r & 1 ? wb & 0xffff0000u : wb << 16);
+                        rv[r] = __uint_as_float(r & 1 ? wr & 0xffff0000u : wr << 16);
                     }
-                    st16(epilogue_dst<EPI>(g, m, n), ow);
-                } else {
-                    epilogue_store<bf16_t, EPI>(g, m, n, v);
-                    if (n + 4 < g.N) epilogue_store<bf16_t, EPI>(g, m, n + 4, v + 4);
+                    epilogue_math<EPI>(v + 4 * h, bv);
+                    if constexpr (epi_resid(EPI)) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) v[4 * h + r] += rv[r];
+                    }
+                    ow.w[2 * h] = pack_bf16x2(v[4 * h], v[4 * h + 1]);
+                    ow.w[2 * h + 1] = pack_bf16x2(v[4 * h + 2], v[4 * h + 3]);
                 }
+                st16(epilogue_dst<EPI>(g, m, n), ow);
+            } else {
+                epilogue_store<bf16_t, EPI>(g, m, n, v);
+                if (n + 4 < g.N) epilogue_store<bf16_t, EPI>(g, m, n + 4, v + 4);
             }
         }
         __syncthreads();
