@@ -150,13 +150,6 @@ __device__ __forceinline__ void wait_vmcnt() {
 // barrier after which other waves overwrite LDS that this one has read.
 __device__ __forceinline__ void wait_all() { __builtin_amdgcn_s_waitcnt(0x0070); }
 
-// The same with up to N vector-memory accesses left in flight.
-template <int N>
-__device__ __forceinline__ void wait_vm_lds() {
-    static_assert(N >= 0 && N < 64, "vmcnt range");
-    __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
-}
-
 // Workgroup barrier without the memory fence of __syncthreads (callers order
 // their own memory operations with explicit waits).
 // The empty asm statements keep the compiler from moving memory accesses
