@@ -441,7 +441,7 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
         }
     };
     // online softmax in place: sacc becomes the weights; running maxima and accumulators updated
-    auto softmax = [&](f32x4_t (&sacc)[2][4]) {
+    auto softmax = [&](f32x4_t (&sacc)[2][4], bool first) {
         // Rescale only when some score exceeds its query's running maximum by
         // more than 8 in the exp2 domain: below that the stale maximum
         // keeps the weights <= 256, exact in bf16 and fp32 alike, and numerator
@@ -466,9 +466,11 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
                 const float was = none ? -INFINITY : m_run[qb] + negm[qb][0];
                 const float up = fmaxf(rm, was);
                 const bool still = up == -INFINITY;   // weights exp2(-inf) = 0
-                const float corr = none ? 0.f : fast_exp2((was - up) * cs);
+                if (!first) {   // nothing summed yet
+                    const float corr = none ? 0.f : fast_exp2((was - up) * cs);
 #pragma unroll
-                for (int h = 0; h < C::NHS; ++h) oacc[qb][h] *= corr;
+                    for (int h = 0; h < C::NHS; ++h) oacc[qb][h] *= corr;
+                }
                 m_run[qb] = fmaxf(m_run[qb], rm - negm[qb][0]);
                 const float n = m_run[qb] == -INFINITY ? 0.f : -fminf(fmaxf(m_run[qb], -kStartMax), kStartMax);
                 negm[qb] = f32x4_t{n, n, n, n};
@@ -555,7 +557,7 @@ __global__ __launch_bounds__(kThreads, dma_occupancy(HD)) void attention_dma_ker
         const int kt = kt0 + t;
         if (!active) continue;   // every row of this wave lies past the segment: it only copies
         qk((t % S) * C::STAGEB, kt * kKeyTile, kt >= kfull, sa);
-        softmax(sa);
+        softmax(sa, t == 0);
         pv((t % S) * C::STAGEB, sa);
     }
 
