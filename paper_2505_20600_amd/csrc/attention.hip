@@ -228,8 +228,8 @@ __device__ __forceinline__ f32x4_t mfma32(bf16x8_t a, bf16x8_t b, f32x4_t c) {
 // 104, ...) stay two-way. The transpose reads take 4 rows x 32 bytes per
 // 16-lane group, which v_swz keeps apart for rows of 128 and 256 bytes.
 //
-// What bounds it: at two or three workgroups per CU the matrix cores are busy
-// 40-50% of the time, the rest is the softmax (per 64-key tile and wave 32
+// What bounds it: at two or three workgroups per CU the matrix cores are busy 37%
+// (head_dim 72, 4096 rows) to 46% (128, a 19-block stack) of the time, the rest is the softmax (per 64-key tile and wave 32
 // exponentials at 8.6 cycles and ~110 other VALU instructions at 3-5, against
 // 576 MFMA cycles at head_dim 64 and 1088 at 128), of which only a part runs
 // under another wave's MFMAs, and the start and end of each workgroup. The
@@ -256,7 +256,8 @@ struct DmaCfg {
     // 32-deep QK steps; the last one's padding slots multiply zeros by zeros.
     // (A 16-deep MFMA for a short remainder takes the same 16 cycles, and one
     // that continued the accumulators of a 32-deep one right before it gave a
-    // query block wrong scores now and then: 390 of 1500 runs at head_dim 48.)
+    // query block wrong scores now and then, 390 of 1500 runs at head_dim 48; the
+    // cause was not found, so that form is not used.)
     static constexpr int NK32 = (HD + 31) / 32;
     static constexpr int ROWB = HD * 2;                 // bytes per K / V row
     static constexpr bool SWZ = ROWB == 128 || ROWB == 256;   // V rows swizzled
